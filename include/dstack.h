@@ -677,12 +677,14 @@ dstack_status dstack_op_conv2d(const void* x, int N, int H, int W, int C, const 
  *   LSTM's input projections as 1x1 convolutions over T*batch pixels with an
  *   fp32 output); fills at most max_convs, *n_convs = the total. */
 typedef struct {
-  int kernel;          /* 0: tiled implicit GEMM; 1: streaming 1x1 (C <= 32) */
+  int kernel;          /* 0: tiled implicit GEMM; 1: streaming 1x1 (C <= 32); 2: 3x3 stride 1 with the tile's
+                          input pixels kept in LDS (C % 64 == 0, K % 8 == 0, bf16 output; a y that is not
+                          16-byte aligned runs kernel 0 instead) */
   int mode;            /* activation addressing: 0 1x1 strided, 1 C % 64 == 0, 2 general, 3 1x1 stride 1 */
   int tile_n, tile_m;  /* output channels x output pixels per workgroup (kernel 1: channels per wave, 0) */
   int splits;          /* depth slices (1: no split) */
   int tiles_per_split; /* 64-deep depth tiles per slice */
-  int stages;          /* LDS ring depth (kernel 0) */
+  int stages;          /* LDS ring depth (kernels 0 and 2) */
   int pad;
   size_t workspace_bytes;
 } dstack_conv_plan;

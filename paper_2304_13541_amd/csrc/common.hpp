@@ -121,8 +121,9 @@ constexpr int SPLITK_TILE_COUNTERS = 4096;
 // The launch a convolution gets: kernel 0 = the tiled implicit GEMM (tile
 // bn x bm, split-K slices of kt_per_split depth tiles, an LDS ring of
 // `stages` tiles, activation addressing `mode`), 1 = the streaming 1x1
-// kernel of small depth (bn = channels per wave); split_bytes = fp32 slice
-// bytes of a split plan (0 without a split).
+// kernel of small depth (bn = channels per wave), 2 = the 3x3 stride-1 kernel
+// that keeps the input pixels of a tile in LDS; split_bytes = fp32 slice bytes
+// of a split plan (0 without a split).
 struct ConvLaunchPlan {
   int kernel, mode, bn, bm, splits, kt_per_split, stages;
   size_t split_bytes;

@@ -33,12 +33,11 @@
 // depth tiles and writes raw fp32 partial sums to a workspace; the last block
 // of each tile to finish (a per-tile arrival counter) sums the slices and
 // applies the epilogue, so no second kernel is launched.
-#include <hip/hip_ext.h>
-
 #include <mutex>
 #include <type_traits>
 
 #include "common.hpp"
+#include "conv_common.hpp"
 
 namespace dstack {
 
@@ -61,115 +60,10 @@ struct ConvArgs {
   FastDiv div_wo, div_ho, div_c, div_s, div_tn;
 };
 
-constexpr int BK = 64;          // depth per LDS stage (bf16 elements)
-constexpr int ROW_BYTES = 128;  // one tile row = BK bf16
-constexpr unsigned OOB = 0x80000000u;  // buffer offset past any tensor (< 2 GB): loads zeros
-constexpr int CPOL_SC1 = 16;           // buffer cache-policy bit: device scope (past the per-XCD L2)
-
 // Addressing of the activation operand: 1x1 stride 1 (the pixel row is the
 // input row), 1x1 strided, C % 64 == 0 (a depth tile lies in one (r, s)), or
 // the general per-chunk (r, s, c) decomposition.
 enum ConvMode { MODE_1X1 = 0, MODE_TILED = 1, MODE_GENERIC = 2, MODE_1X1S1 = 3 };
-
-__device__ __forceinline__ void store_out4(void* y, bool f32, long idx, const float v[4]) {
-  if (f32) {
-    f32x4 o = {v[0], v[1], v[2], v[3]};
-    *reinterpret_cast<f32x4*>(reinterpret_cast<float*>(y) + idx) = o;
-  } else {
-    bf16x4 o = {(bf16)v[0], (bf16)v[1], (bf16)v[2], (bf16)v[3]};
-    *reinterpret_cast<bf16x4*>(reinterpret_cast<bf16*>(y) + idx) = o;
-  }
-}
-
-// vmcnt wait with an immediate count (gfx9 encoding: vmcnt[3:0] | vmcnt[5:4] << 14,
-// expcnt and lgkmcnt left at "no wait").
-template <int N>
-__device__ __forceinline__ void wait_vmcnt() {
-  static_assert(N >= 0 && N < 64, "vmcnt is 6 bits");
-  __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | (7 << 4) | (15 << 8));
-}
-
-typedef __attribute__((__vector_size__(4 * sizeof(int)))) int i32x4;
-
-// Raw buffer descriptor: base, no stride, num_records = byte size (offsets at
-// or past it read as zero), gfx9 data-format word.
-__device__ __forceinline__ i32x4 make_rsrc(const void* base, unsigned bytes) {
-  const unsigned long long p = (unsigned long long)base;
-  i32x4 r;
-  r[0] = (int)(unsigned)(p & 0xffffffffu);
-  r[1] = (int)(unsigned)((p >> 32) & 0xffffu);
-  r[2] = (int)bytes;
-  r[3] = 0x00020000;
-  return r;
-}
-
-// 32-bit LDS byte address of a pointer into a __shared__ array.
-__device__ __forceinline__ unsigned lds_address(const void* p) {
-  return (unsigned)(unsigned long long)(const __attribute__((address_space(3))) void*)p;
-}
-
-// NL wave-loads of 16 bytes per lane: load j moves buffer offsets off[j]
-// into LDS at lds_base + 1024 * j + 16 * lane.  Issued as inline asm so that
-// the compiler does not treat every later LDS read as dependent on it (it
-// would wait for all loads in flight); the kernel's own vmcnt waits order
-// these loads against the LDS reads.  M0 (the LDS destination) is saved once,
-// stepped by 1 KB between loads (one wait state after each write), restored.
-template <int NL>
-__device__ __forceinline__ void load_group(i32x4 rsrc, const unsigned (&off)[NL], unsigned lds_base);
-
-template <>
-__device__ __forceinline__ void load_group<1>(i32x4 rsrc, const unsigned (&off)[1], unsigned lds_base) {
-  unsigned saved;
-  asm volatile(
-      "s_mov_b32 %0, m0\n\t"
-      "s_mov_b32 m0, %1\n\t"
-      "s_nop 0\n\t"
-      "buffer_load_dwordx4 %2, %3, 0 offen lds\n\t"
-      "s_mov_b32 m0, %0"
-      : "=&s"(saved)
-      : "s"(lds_base), "v"(off[0]), "s"(rsrc)
-      : "memory");
-}
-
-template <>
-__device__ __forceinline__ void load_group<2>(i32x4 rsrc, const unsigned (&off)[2], unsigned lds_base) {
-  unsigned saved;
-  asm volatile(
-      "s_mov_b32 %0, m0\n\t"
-      "s_mov_b32 m0, %1\n\t"
-      "s_nop 0\n\t"
-      "buffer_load_dwordx4 %2, %4, 0 offen lds\n\t"
-      "s_add_u32 m0, m0, 0x400\n\t"
-      "s_nop 0\n\t"
-      "buffer_load_dwordx4 %3, %4, 0 offen lds\n\t"
-      "s_mov_b32 m0, %0"
-      : "=&s"(saved)
-      : "s"(lds_base), "v"(off[0]), "v"(off[1]), "s"(rsrc)
-      : "memory", "scc");
-}
-
-template <>
-__device__ __forceinline__ void load_group<4>(i32x4 rsrc, const unsigned (&off)[4], unsigned lds_base) {
-  unsigned saved;
-  asm volatile(
-      "s_mov_b32 %0, m0\n\t"
-      "s_mov_b32 m0, %1\n\t"
-      "s_nop 0\n\t"
-      "buffer_load_dwordx4 %2, %6, 0 offen lds\n\t"
-      "s_add_u32 m0, m0, 0x400\n\t"
-      "s_nop 0\n\t"
-      "buffer_load_dwordx4 %3, %6, 0 offen lds\n\t"
-      "s_add_u32 m0, m0, 0x400\n\t"
-      "s_nop 0\n\t"
-      "buffer_load_dwordx4 %4, %6, 0 offen lds\n\t"
-      "s_add_u32 m0, m0, 0x400\n\t"
-      "s_nop 0\n\t"
-      "buffer_load_dwordx4 %5, %6, 0 offen lds\n\t"
-      "s_mov_b32 m0, %0"
-      : "=&s"(saved)
-      : "s"(lds_base), "v"(off[0]), "v"(off[1]), "v"(off[2]), "v"(off[3]), "s"(rsrc)
-      : "memory", "scc");
-}
 
 template <int BN, int BM, int WN, int WM, int STAGES, int MODE, bool OUT_F32, bool SPLIT>
 __global__ __launch_bounds__(256) void conv_igemm_kernel(ConvArgs a) {
@@ -520,16 +414,6 @@ __global__ __launch_bounds__(256) void conv_igemm_kernel(ConvArgs a) {
     rows([hi](float v) { return fminf(fmaxf(v, 0.0f), hi); });
 }
 
-// 256-thread launch; through hipExtLaunchKernelGGL when dispatch events are
-// armed (and not while launch shapes are being recorded)
-template <typename K, typename... Args>
-static void launch_k(K kernel, dim3 grid, hipStream_t st, hipEvent_t e0, hipEvent_t e1, Args... args) {
-  if ((e0 || e1) && !shape_recorder())
-    hipExtLaunchKernelGGL(kernel, grid, dim3(256), 0, st, e0, e1, 0, args...);
-  else
-    launch(kernel, grid, dim3(256), 0, st, args...);
-}
-
 // 1x1, stride-1 convolution of small depth (C <= 32): a streaming GEMM that
 // stages nothing of its inputs in LDS.  The output (M x K) is many times the
 // input (M x C) and the weights (K x C) are tiny, so the layer is bound by
@@ -670,9 +554,9 @@ static void launch_1x1s_nb(const ConvArgs& a, bool f32, int n_cu, hipStream_t st
   const dim3 grid(bx, chunks);
   const DispatchEvents& de = dispatch_events();
   if (f32)
-    launch_k(conv_igemm_1x1s_kernel<NB, KS, true>, grid, st, de.start, de.stop, a, groups);
+    launch_k(conv_igemm_1x1s_kernel<NB, KS, true>, grid, 256, st, de.start, de.stop, a, groups);
   else
-    launch_k(conv_igemm_1x1s_kernel<NB, KS, false>, grid, st, de.start, de.stop, a, groups);
+    launch_k(conv_igemm_1x1s_kernel<NB, KS, false>, grid, 256, st, de.start, de.stop, a, groups);
 }
 
 // channel blocks per wave: the largest divisor of K / 16 that is at most 8
@@ -699,6 +583,7 @@ static void launch_1x1s(const ConvArgs& a, bool f32, int n_cu, hipStream_t st) {
 
 struct ConvPlan {
   int bn, bm, splits;
+  double cost;  // estimated time, us
 };
 
 // Tile and split choice from the GEMM shape and the CUs of the partition, by
@@ -718,8 +603,6 @@ struct TileCost {
 static constexpr TileCost kTiles[] = {
     {128, 128, 0.65}, {128, 64, 0.485}, {64, 128, 0.50}, {64, 64, 0.42}, {32, 128, 0.25}};
 constexpr double kRampUs = 1.4;
-constexpr double kSliceWriteUs = 2.6;   // device-scope slice stores until acknowledged
-constexpr double kSliceReadUs = 0.75;   // per slice of 8192 fp32 values, the last block's read-back
 
 // Launches whose blocks walk at most kShortTiles depth tiles (split-K
 // slices: at most kShortSplitTiles) run with a two-tile ring, so that more
@@ -750,7 +633,7 @@ static double plan_cost(const TileCost& t, int M, int K, int nkt, int splits, in
   const long bpc = short_ring(per, s, blocks, n_cu) ? short_blocks_per_cu(t.bn, t.bm, s > 1) : 2;
   const long rounds = (blocks + bpc * n_cu - 1) / (bpc * n_cu);
   double blk = kRampUs + per * t.step_us + 0.6 + 1.5 * (t.bn * t.bm) / 16384.0;
-  if (s > 1) blk += kSliceWriteUs + kSliceReadUs * s * (t.bn * t.bm) / 8192.0;
+  if (s > 1) blk += CONV_SLICE_WRITE_US + CONV_SLICE_READ_US * s * (t.bn * t.bm) / 8192.0;
   return (double)rounds * blk;
 }
 
@@ -758,18 +641,15 @@ static ConvPlan choose_plan(int M, int K, int Kg, int n_cu, bool can_split, size
   // channel tiles: 32 for K <= 32, 64 for K <= 64, else 64 or 128
   const int bn_min = K <= 32 ? 32 : 64, bn_max = K <= 32 ? 32 : (K <= 64 ? 64 : 128);
   const int nkt = ceil_div(Kg, BK);
-  ConvPlan best{bn_max, 128, 1};
-  double best_t = 1e30;
+  ConvPlan best{bn_max, 128, 1, 1e30};
   for (const TileCost& t : kTiles) {
     if (t.bn < bn_min || t.bn > bn_max) continue;
     for (int sp = 1; sp <= 16; sp *= 2) {
       if (sp > 1 && (!can_split || nkt / sp < 2 || (size_t)sp * M * K * sizeof(float) > split_bytes)) break;
       if (sp > 1 && (long)ceil_div(M, t.bm) * ceil_div(K, t.bn) > SPLITK_TILE_COUNTERS) break;
       const double c = plan_cost(t, M, K, nkt, sp, n_cu);
-      if (c < best_t * 0.97) {  // a split or a smaller tile must win by more than 3%
-        best_t = c;
-        best = ConvPlan{t.bn, t.bm, sp};
-      }
+      // a split or a smaller tile must win by more than 3%
+      if (c < best.cost * 0.97) best = ConvPlan{t.bn, t.bm, sp, c};
     }
   }
   return best;
@@ -801,17 +681,17 @@ static void launch_mode(ConvArgs a, bool f32, int splits, int stages, hipStream_
   hipEvent_t e0 = de.start, e1 = de.stop;
   if (STAGES > 2 && stages == 2) {
     if (splits > 1)
-      launch_k(conv_igemm_kernel<BN, BM, WN, WM, 2, MODE, false, true>, grid, st, e0, e1, a);
+      launch_k(conv_igemm_kernel<BN, BM, WN, WM, 2, MODE, false, true>, grid, 256, st, e0, e1, a);
     else if (f32)
-      launch_k(conv_igemm_kernel<BN, BM, WN, WM, 2, MODE, true, false>, grid, st, e0, e1, a);
+      launch_k(conv_igemm_kernel<BN, BM, WN, WM, 2, MODE, true, false>, grid, 256, st, e0, e1, a);
     else
-      launch_k(conv_igemm_kernel<BN, BM, WN, WM, 2, MODE, false, false>, grid, st, e0, e1, a);
+      launch_k(conv_igemm_kernel<BN, BM, WN, WM, 2, MODE, false, false>, grid, 256, st, e0, e1, a);
   } else if (splits > 1)
-    launch_k(conv_igemm_kernel<BN, BM, WN, WM, STAGES, MODE, false, true>, grid, st, e0, e1, a);
+    launch_k(conv_igemm_kernel<BN, BM, WN, WM, STAGES, MODE, false, true>, grid, 256, st, e0, e1, a);
   else if (f32)
-    launch_k(conv_igemm_kernel<BN, BM, WN, WM, STAGES, MODE, true, false>, grid, st, e0, e1, a);
+    launch_k(conv_igemm_kernel<BN, BM, WN, WM, STAGES, MODE, true, false>, grid, 256, st, e0, e1, a);
   else
-    launch_k(conv_igemm_kernel<BN, BM, WN, WM, STAGES, MODE, false, false>, grid, st, e0, e1, a);
+    launch_k(conv_igemm_kernel<BN, BM, WN, WM, STAGES, MODE, false, false>, grid, 256, st, e0, e1, a);
 }
 
 template <int BN, int BM, int WN, int WM>
@@ -854,7 +734,27 @@ static dstack_status conv_shape(int N, int H, int W, int C, int K, int R, int S,
 // kernel with its tile, split and ring depth.  Split-K is considered only
 // with a workspace and arrival counters, and not for an fp32 output (the
 // fused reduction stores bf16).
-static ConvLaunchPlan conv_launch_plan(const ConvArgs& a, bool out_fp32, bool can_split, size_t split_bytes) {
+//
+// 3x3 layers of stride 1 with whole 64-channel chunks may take the kernel
+// that keeps the tile's input pixels in LDS (`halo`, which a caller whose
+// output is not 16-byte aligned leaves out: that kernel stores 16 bytes at a
+// time).  The estimates are compared after a correction of the general
+// kernel's, which is about 15% low unsplit (estimate against measured less a
+// launch gap of 1.3 us: 11.5 / 12.1 to 15.2 / 19.7 us) and high for split
+// 64 x 64 tiles (10.9 / 7.6 to 14.0 / 11.4 us); the halo kernel's are within
+// 5%.  The general kernel keeps partitions of fewer than 64 CUs, fp32
+// outputs, and the shapes whose split plan needs more than 32 MiB of slices
+// (the allocation-free entry point refuses those).
+constexpr int kHaloMinCus = 64;
+static double general_correction(const ConvPlan& p, const ConvArgs& a) {
+  if (p.splits > 1) return p.bn * p.bm <= 64 * 64 ? 0.75 : 1.0;
+  // over many rounds the two blocks of a CU drift apart and overlap
+  // (32 images of 112x112x128 -> 128 on 256 CUs: 127 us against 131)
+  const long rounds = (long)ceil_div(a.M, p.bm) * ceil_div(a.K, p.bn) / (2L * a.n_cu);
+  return rounds > 4 ? 1.05 : 1.15;
+}
+static ConvLaunchPlan conv_launch_plan(const ConvArgs& a, bool out_fp32, bool can_split, size_t split_bytes,
+                                       HaloPlan* halo = nullptr) {
   ConvLaunchPlan L{};
   const bool one = a.R == 1 && a.S == 1 && a.pad == 0;
   if (one && a.stride == 1 && a.C <= 32 && a.K % 16 == 0 && a.act <= ACT_RELU6) {  // small depth: streaming
@@ -869,6 +769,17 @@ static ConvLaunchPlan conv_launch_plan(const ConvArgs& a, bool out_fp32, bool ca
   L.kernel = 0;
   L.mode = one ? (a.stride == 1 ? MODE_1X1S1 : MODE_1X1) : (a.C % BK == 0 && a.R * a.S <= 32 ? MODE_TILED : MODE_GENERIC);
   const ConvPlan p = choose_plan(a.M, a.K, a.Kg, a.n_cu, can_split && !out_fp32, split_bytes);
+  if (halo && a.R == 3 && a.S == 3 && a.stride == 1 && a.pad == 1 && a.C % BK == 0 && a.K % 8 == 0 && !out_fp32 &&
+      a.n_cu >= kHaloMinCus && (p.splits == 1 || (size_t)p.splits * a.M * a.K * sizeof(float) <= ((size_t)32 << 20)) &&
+      halo_plan(a.N, a.H, a.W, a.C, a.K, a.n_cu, can_split, split_bytes, halo) &&
+      halo->cost < general_correction(p, a) * p.cost) {
+    L.kernel = 2;
+    L.mode = MODE_TILED;
+    halo_tile(*halo, &L.bn, &L.bm, &L.stages);
+    L.splits = halo->splits;
+    L.kt_per_split = halo->chunks_per_split * 9;
+    return L;
+  }
   const int nkt = ceil_div(a.Kg, BK);
   L.kt_per_split = ceil_div(nkt, p.splits);
   L.splits = ceil_div(nkt, L.kt_per_split);  // no empty slices
@@ -885,7 +796,8 @@ dstack_status conv2d_plan(int N, int H, int W, int C, int K, int R, int S, int s
   ConvArgs a{};
   dstack_status s = conv_shape(N, H, W, C, K, R, S, stride, pad, act, n_cu, &a);
   if (s != DSTACK_OK) return s;
-  *out = conv_launch_plan(a, out_fp32, true, split_bytes);
+  HaloPlan halo;
+  *out = conv_launch_plan(a, out_fp32, true, split_bytes, &halo);
   out->split_bytes = out->splits > 1 ? (size_t)out->splits * a.M * a.K * sizeof(float) : 0;
   return DSTACK_OK;
 }
@@ -903,8 +815,16 @@ dstack_status launch_conv2d_ws(const bf16* x, int N, int H, int W, int C, const 
   a.div_ho = FastDiv::make(a.Ho);
   a.div_c = FastDiv::make(C);
   a.div_s = FastDiv::make(S);
+  HaloPlan halo;
+  const bool can_split = splitk_ws != nullptr && tile_counters != nullptr;
   const ConvLaunchPlan p =
-      conv_launch_plan(a, out_fp32, splitk_ws != nullptr && tile_counters != nullptr, splitk_bytes);
+      conv_launch_plan(a, out_fp32, can_split, splitk_bytes, ((uintptr_t)y & 15) == 0 ? &halo : nullptr);
+  if (p.kernel == 2) {
+    launch_halo(x, N, H, W, C, w, K, scale, shift, res, act, static_cast<bf16*>(y), halo, splitk_ws, tile_counters,
+                st);
+    DS_HIP(hipGetLastError());
+    return DSTACK_OK;
+  }
   if (p.kernel == 1) {
     launch_1x1s(a, out_fp32, a.n_cu, st);
     DS_HIP(hipGetLastError());

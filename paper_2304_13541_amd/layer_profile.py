@@ -112,7 +112,7 @@ def sweep():
 
 
 def kernel_class(name):
-    for key, cls in (("probe_kernel", "marker"), ("conv_igemm_1x1s", "conv_1x1_stream"), ("conv_igemm", "conv"),
+    for key, cls in (("probe_kernel", "marker"), ("conv_igemm_1x1s", "conv_1x1_stream"), ("conv_igemm", "conv"), ("conv_halo", "conv"),
                      ("conv_rgb", "stem"), ("expand_dw", "expand_dw"), ("dwconv3x3", "dwconv3x3"),
                      ("fc_reduce", "fc"), ("fc_kernel", "fc"), ("lstm_step", "lstm_step"), ("maxpool", "pool"),
                      ("avgpool", "pool")):
