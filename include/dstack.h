@@ -137,7 +137,7 @@ typedef struct {
   int out_features;         /* CNN, transformer: classes (fp32 logits); LSTM: hidden (fp32 h) */
   int num_tensors;
   int64_t num_params;
-  int num_kernels;          /* kernel launches per forward */
+  int num_kernels;          /* kernel launches per forward (LSTM: where it runs step by step) */
   double flops_per_item;    /* algorithmic FLOPs (2 per MAC) per inference */
   double mfma_flops_per_item; /* of which in MFMA convolution/GEMM kernels */
   double weight_bytes;      /* bf16 weights read per forward */
@@ -650,8 +650,15 @@ dstack_status dstack_serve(const dstack_model* models, int n_models, const void*
  *   aligned, caller owned) needs lstm_workspace_bytes(T, B, H) bytes: the
  *   input projections, the cell state, and copies of W_hh and of h(t-1) in
  *   the recurrent product's fragment order (W_hh is repacked on each call).
- *   The recurrent step's launch (hidden units per workgroup) is chosen for
- *   the CUs of the stream's CU mask; the result does not depend on it. */
+ *   With 4 or more steps, and CUs enough in the stream's CU mask to hold W_hh
+ *   in their registers, the recurrence runs in one launch whose workgroups
+ *   exchange h through the workspace; else one launch per step, its shape
+ *   (hidden units per workgroup) chosen for those CUs.  The result is the same
+ *   up to fp32 summation order.
+ * lstm_layer_wait: lstm_layer with the time (us; 5000 there) that a workgroup
+ *   of the one launch waits for the others' h.  Past it (other work holds the
+ *   CUs so that not all of them run) one workgroup computes the sequence
+ *   alone, tens of times slower; a negative value takes that path at once. */
 dstack_status dstack_op_conv2d(const void* x, int N, int H, int W, int C, const void* w, int K, int R, int S,
                                int stride, int pad, const float* scale, const float* shift, const void* res, int act,
                                void* y, int out_fp32, void* stream);
@@ -748,6 +755,9 @@ dstack_status dstack_op_avgpool(const void* x, int N, int H, int W, int C, void*
 size_t dstack_lstm_workspace_bytes(int T, int B, int H);
 dstack_status dstack_op_lstm_layer(const void* x, int T, int B, int I, int H, const void* w_ih, const void* w_hh,
                                    const float* bias, void* h_bf16, float* h_f32, void* workspace, void* stream);
+dstack_status dstack_op_lstm_layer_wait(const void* x, int T, int B, int I, int H, const void* w_ih,
+                                        const void* w_hh, const float* bias, void* h_bf16, float* h_f32,
+                                        void* workspace, int wait_us, void* stream);
 /* Transformer kernels (the BERT encoder of Sec. 4.4's transformer workload).
  * embed_ln: for each of `rows` tokens (ids int32 [rows], position = row %
  *   T, token type 0): e = we[id] + pe[row % T] + te[0] (tables bf16

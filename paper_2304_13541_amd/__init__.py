@@ -212,6 +212,7 @@ _SIGS = {
     "dstack_op_embed_ln": ([_vp, _i, _i, _i, _vp, _vp, _vp, _i, _vp, _vp, ctypes.c_float, _vp, _vp], _i),
     "dstack_op_layernorm": ([_vp, _i, _i, _vp, _vp, ctypes.c_float, _vp, _vp], _i),
     "dstack_op_attention": ([_vp, _i, _i, _i, _i, _vp, _vp], _i),
+    "dstack_op_lstm_layer_wait": ([_vp, _i, _i, _i, _i, _vp, _vp, _vp, _vp, _vp, _vp, _i, _vp], _i),
     "dstack_op_lstm_layer": ([_vp, _i, _i, _i, _i, _vp, _vp, _vp, _vp, _vp, _vp, _vp], _i),
 }
 
@@ -694,9 +695,14 @@ def lstm_workspace_bytes(T, B, H):
     return lib().dstack_lstm_workspace_bytes(T, B, H)
 
 
-def lstm_layer(x, w_ih, w_hh, bias, h_bf16, h_f32, workspace, stream=None):
+def lstm_layer(x, w_ih, w_hh, bias, h_bf16, h_f32, workspace, stream=None, wait_us=None):
+    """wait_us: see dstack_op_lstm_layer_wait (None: the default)."""
     T, B, I = x.shape
     H = w_hh.shape[1]
+    if wait_us is not None:
+        _check(lib().dstack_op_lstm_layer_wait(_ptr(x), T, B, I, H, _ptr(w_ih), _ptr(w_hh), _ptr(bias), _ptr(h_bf16),
+                                               _ptr(h_f32), _ptr(workspace), int(wait_us), _stream(stream)))
+        return
     _check(lib().dstack_op_lstm_layer(_ptr(x), T, B, I, H, _ptr(w_ih), _ptr(w_hh), _ptr(bias), _ptr(h_bf16),
                                       _ptr(h_f32), _ptr(workspace), _stream(stream)))
 

@@ -1005,8 +1005,9 @@ dstack_status dstack_op_avgpool(const void* x, int N, int H, int W, int C, void*
   });
 }
 
-// gx [T][B][4H] fp32 | c [B][H] fp32 | W_hh in fragment order [4H][H] bf16 |
-// h(t-1), h(t) in fragment order [2][B][H] bf16, each part 256-byte aligned
+// gx [T][B][4H] fp32 | c [B][H] fp32 | W_hh in fragment order [4H][H] bf16, or
+// the blocks' exchange of h (at most 4 (B + 1) H bytes) | h(t-1), h(t) in
+// fragment order [2][B][H] bf16, or two control words; each part 256-byte aligned
 static size_t align256z(size_t n) { return (n + 255) / 256 * 256; }
 size_t dstack_lstm_workspace_bytes(int T, int B, int H) {
   if (T <= 0 || B <= 0 || H <= 0) return 0;
@@ -1014,8 +1015,9 @@ size_t dstack_lstm_workspace_bytes(int T, int B, int H) {
          (size_t)2 * B * H * 2;
 }
 
-dstack_status dstack_op_lstm_layer(const void* x, int T, int B, int I, int H, const void* w_ih, const void* w_hh,
-                                   const float* bias, void* h_bf16, float* h_f32, void* workspace, void* stream) {
+dstack_status dstack_op_lstm_layer_wait(const void* x, int T, int B, int I, int H, const void* w_ih, const void* w_hh,
+                                        const float* bias, void* h_bf16, float* h_f32, void* workspace, int wait_us,
+                                        void* stream) {
   return guarded([&] {
     DS_CHECK(x && w_ih && w_hh && bias && h_bf16 && workspace, DSTACK_E_INVALID, "lstm_layer: null pointer");
     DS_CHECK(T >= 1 && I % 8 == 0 && I > 0, DSTACK_E_UNSUPPORTED, "lstm_layer: T >= 1, I % 8 == 0");
@@ -1031,8 +1033,15 @@ dstack_status dstack_op_lstm_layer(const void* x, int T, int B, int I, int H, co
     bf16* hp = reinterpret_cast<bf16*>(p);
     return lstm_layer_run(static_cast<const bf16*>(x), T, B, I, H, static_cast<const bf16*>(w_ih),
                           static_cast<const bf16*>(w_hh), nullptr, bias, static_cast<bf16*>(h_bf16), h_f32, gx, c,
-                          wp, hp, stream_cu_count((hipStream_t)stream), (hipStream_t)stream, nullptr);
+                          wp, hp, wp, reinterpret_cast<unsigned*>(hp), wait_us * 100L,
+                          stream_cu_count((hipStream_t)stream), (hipStream_t)stream, nullptr);
   });
+}
+
+dstack_status dstack_op_lstm_layer(const void* x, int T, int B, int I, int H, const void* w_ih, const void* w_hh,
+                                   const float* bias, void* h_bf16, float* h_f32, void* workspace, void* stream) {
+  return dstack_op_lstm_layer_wait(x, T, B, I, H, w_ih, w_hh, bias, h_bf16, h_f32, workspace,
+                                   (int)(LSTM_SEQ_LIMIT / 100), stream);
 }
 
 dstack_status dstack_op_embed_ln(const int32_t* ids, int rows, int T, int vocab, const void* we, const void* pe,

@@ -172,6 +172,19 @@ dstack_status launch_lstm_pack_whh(const bf16* w_hh, bf16* wp, int H, hipStream_
 dstack_status launch_lstm_step(const float* gx_t, const bf16* wp, const bf16* hp_prev, float* c, bf16* h_next,
                                bf16* hp_next, float* h_f32, int B, int H, bool first, int n_cu, hipStream_t st);
 int lstm_units_per_block(int B, int H, int n_cu);
+// The recurrence of a whole sequence in one launch (plus one that clears its
+// exchange buffers): `groups` batch slices, row_tiles row tiles of W_hh per
+// block.  false: this shape on these CUs takes one launch per step.
+struct LstmSeqPlan {
+  int groups, row_tiles, blocks;
+};
+bool lstm_seq_plan(int T, int B, int H, int n_cu, hipStream_t st, LstmSeqPlan* out);
+size_t lstm_seq_exchange_bytes(int B, int H, const LstmSeqPlan& p);  // <= 4 (B + 1) H
+// whh row-major; c: [B][H] scratch; ctl: two words; limit: how long a block
+// waits for the others' h, in ticks of 10 ns (negative: gives up at once).
+constexpr long LSTM_SEQ_LIMIT = 500000;
+dstack_status launch_lstm_seq(const float* gx, const bf16* whh, bf16* h, float* hf, float* c, void* exchange,
+                              unsigned* ctl, int T, int B, int H, const LstmSeqPlan& p, long limit, hipStream_t st);
 dstack_status launch_probe(uint32_t* d_out, int n_blocks, hipStream_t st);
 
 }  // namespace dstack

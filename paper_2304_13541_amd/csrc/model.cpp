@@ -680,7 +680,7 @@ dstack_status get_workspace(Model& m, int pid, int n_cu, hipStream_t st, Workspa
   total += align256(sk);
   const size_t cnt_off = total;
   if (sk) total += align256(SPLITK_TILE_COUNTERS * sizeof(unsigned));
-  size_t gx_off = 0, c_off = 0, h0_off = 0, h1_off = 0, hp_off = 0;
+  size_t gx_off = 0, c_off = 0, h0_off = 0, h1_off = 0, hp_off = 0, ctl_off = 0;
   if (m.is_lstm) {
     gx_off = total;
     total += align256((size_t)m.lstm_T * m.max_batch * 4 * m.lstm_H * 4);
@@ -692,6 +692,8 @@ dstack_status get_workspace(Model& m, int pid, int n_cu, hipStream_t st, Workspa
     total += align256((size_t)m.lstm_T * m.max_batch * m.lstm_H * 2);
     hp_off = total;
     total += align256((size_t)2 * m.max_batch * m.lstm_H * 2);
+    ctl_off = total;
+    total += 256;
   }
   DS_HIP(hipMalloc(&w->base, total));
   w->bytes = total;
@@ -717,6 +719,7 @@ dstack_status get_workspace(Model& m, int pid, int n_cu, hipStream_t st, Workspa
     w->lstm_h[0] = (bf16*)(base + h0_off);
     w->lstm_h[1] = (bf16*)(base + h1_off);
     w->lstm_hp = (bf16*)(base + hp_off);
+    w->lstm_ctl = (unsigned*)(base + ctl_off);
   }
   *out = w.get();
   m.ws[pid] = std::move(w);
@@ -796,7 +799,8 @@ static double conv_bytes(const Op& op, int b) {
 
 dstack_status lstm_layer_run(const bf16* x, int T, int B, int I, int H, const bf16* w_ih, const bf16* w_hh,
                              const bf16* whh_packed, const float* bias, bf16* h_bf16, float* h_f32, float* gx,
-                             float* c, bf16* wp_scratch, bf16* hp, int n_cu, hipStream_t st, KernelTimer* timer) {
+                             float* c, bf16* wp_scratch, bf16* hp, void* exchange, unsigned* ctl, long wait_limit,
+                             int n_cu, hipStream_t st, KernelTimer* timer) {
   // input projection of all steps at once: gx[t*B + b][:] = W_ih x + b_ih + b_hh (fp32)
   if (timer) timer->before();
   dstack_status s = launch_conv2d_ws(x, T * B, 1, 1, I, w_ih, 4 * H, 1, 1, 1, 0, nullptr, bias, nullptr, ACT_NONE,
@@ -805,6 +809,16 @@ dstack_status lstm_layer_run(const bf16* x, int T, int B, int I, int H, const bf
   if (timer)
     timer->after(KC_MFMA, 2.0 * T * B * I * 4.0 * H,
                  (double)T * B * I * 2 + 4.0 * H * I * 2 + (double)T * B * 4 * H * 4, T * B, 4 * H, I);
+  LstmSeqPlan seq;
+  if (lstm_seq_plan(T, B, H, n_cu, st, &seq)) {
+    if (timer) timer->before();
+    s = launch_lstm_seq(gx, w_hh, h_bf16, h_f32, c, exchange, ctl, T, B, H, seq, wait_limit, st);
+    if (s != DSTACK_OK) return s;
+    if (timer)
+      timer->after(KC_LSTM, 2.0 * T * B * H * 4.0 * H,
+                   4.0 * H * H * 2 + (double)T * B * (4.0 * H * 4 + H * 2.0 + (h_f32 ? H * 4.0 : 0.0)), B, 4 * H, H);
+    return DSTACK_OK;
+  }
   // W_hh in the fragment order of the recurrent product
   const bf16* wp = whh_packed;
   if (!wp) {
@@ -852,7 +866,8 @@ dstack_status forward(Model& m, int batch, const void* d_in, void* d_out, Worksp
       bf16* hb = op.in == BUF_IN ? ws.lstm_h[0] : ws.lstm_h[1];
       float* hf = op.out == BUF_OUT ? (float*)d_out : nullptr;
       s = lstm_layer_run(x, op.T, batch, op.I, op.Hd, m.d_w + op.wih_off, m.d_w + op.whh_off, m.d_wp + op.wp_off,
-                         f32 + op.bias_off, hb, hf, ws.lstm_gx, ws.lstm_c, nullptr, ws.lstm_hp, n_cu, st, timer);
+                         f32 + op.bias_off, hb, hf, ws.lstm_gx, ws.lstm_c, nullptr, ws.lstm_hp, ws.lstm_hp, ws.lstm_ctl,
+                         LSTM_SEQ_LIMIT, n_cu, st, timer);
       if (s != DSTACK_OK) return s;
       continue;
     }

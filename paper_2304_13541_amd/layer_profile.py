@@ -112,10 +112,10 @@ def sweep():
 
 
 def kernel_class(name):
-    for key, cls in (("probe_kernel", "marker"), ("conv_igemm_1x1s", "conv_1x1_stream"), ("conv_igemm", "conv"), ("conv_halo", "conv"),
-                     ("conv_rgb", "stem"), ("expand_dw", "expand_dw"), ("dwconv3x3", "dwconv3x3"),
-                     ("fc_reduce", "fc"), ("fc_kernel", "fc"), ("lstm_step", "lstm_step"), ("maxpool", "pool"),
-                     ("avgpool", "pool")):
+    for key, cls in (("probe_kernel", "marker"), ("conv_igemm_1x1s", "conv_1x1_stream"), ("conv_igemm", "conv"),
+                     ("conv_halo", "conv"), ("conv_rgb", "stem"), ("expand_dw", "expand_dw"), ("dwconv3x3", "dwconv3x3"),
+                     ("fc_reduce", "fc"), ("fc_kernel", "fc"), ("lstm_step", "lstm_step"),
+                     ("lstm_seq", "lstm_seq"), ("maxpool", "pool"), ("avgpool", "pool")):
         if key in name:
             return cls
     return "other"
