@@ -950,7 +950,8 @@ dstack_status dstack_op_conv2d_rgb(const void* x, int N, int H, int W, const voi
     DS_CHECK(x && w4 && y, DSTACK_E_INVALID, "conv2d_rgb: null pointer");
     DS_CHECK(act >= 0 && act <= 2, DSTACK_E_INVALID, "conv2d_rgb: act must be 0, 1 or 2");
     return launch_conv2d_rgb(static_cast<const bf16*>(x), N, H, W, static_cast<const bf16*>(w4), K, R, stride, pad,
-                             scale, shift, act, static_cast<bf16*>(y), (hipStream_t)stream);
+                             scale, shift, act, static_cast<bf16*>(y),
+                             stream_cu_count((hipStream_t)stream), (hipStream_t)stream);
   });
 }
 

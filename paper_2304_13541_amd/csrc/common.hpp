@@ -37,6 +37,13 @@ typedef __attribute__((__vector_size__(4 * sizeof(__bf16)))) __bf16 bf16x4;
 typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4;
 typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16;
 
+typedef __attribute__((__vector_size__(2 * sizeof(__bf16)))) __bf16 bf16x2;
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+// two floats to round-to-nearest-even bf16 in one packed conversion
+__device__ __forceinline__ unsigned pack_bf16x2(float lo, float hi) {
+  return __builtin_bit_cast(unsigned, __builtin_convertvector((f32x2{lo, hi}), bf16x2));
+}
+
 enum Act { ACT_NONE = 0, ACT_RELU = 1, ACT_RELU6 = 2, ACT_GELU = 3, ACT_TANH = 4 };
 
 // Thread-local error text behind dstack_last_error().
@@ -167,7 +174,7 @@ dstack_status launch_layernorm(const bf16* x, int rows, int H, const float* gamm
                                bf16* y, hipStream_t st);
 dstack_status launch_attention(const bf16* qkv, int B, int T, int heads, int dh, bf16* out, hipStream_t st);
 dstack_status launch_conv2d_rgb(const bf16* x, int N, int H, int W, const bf16* w4, int K, int R, int stride, int pad,
-                                const float* scale, const float* shift, int act, bf16* y, hipStream_t st);
+                                const float* scale, const float* shift, int act, bf16* y, int n_cu, hipStream_t st);
 dstack_status launch_lstm_pack_whh(const bf16* w_hh, bf16* wp, int H, hipStream_t st);
 dstack_status launch_lstm_step(const float* gx_t, const bf16* wp, const bf16* hp_prev, float* c, bf16* h_next,
                                bf16* hp_next, float* h_f32, int B, int H, bool first, int n_cu, hipStream_t st);

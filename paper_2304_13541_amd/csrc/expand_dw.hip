@@ -56,17 +56,8 @@ __device__ __forceinline__ float2 act_bounds(int act) {
   return float2{act == ACT_NONE ? -INFINITY : 0.0f, act == ACT_RELU6 ? 6.0f : INFINITY};
 }
 
-typedef __attribute__((__vector_size__(2 * sizeof(__bf16)))) __bf16 bf16x2;
-
 __device__ __forceinline__ float dot2(unsigned e, bf16x2 w, float acc) {
   return __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, e), w, acc, false);
-}
-
-typedef float f32x2 __attribute__((ext_vector_type(2)));
-
-// two floats to round-to-nearest-even bf16 in one packed conversion
-__device__ __forceinline__ unsigned pack_bf16x2(float lo, float hi) {
-  return __builtin_bit_cast(unsigned, __builtin_convertvector((f32x2{lo, hi}), bf16x2));
 }
 
 template <int CB, int DS, int S>

@@ -892,7 +892,7 @@ dstack_status forward(Model& m, int batch, const void* d_in, void* d_out, Worksp
         break;
       case OP_CONV_RGB:
         s = launch_conv2d_rgb(src, batch, op.H, op.W, m.d_w + op.w_off, op.K, op.R, op.stride, op.pad,
-                              f32 + op.scale_off, f32 + op.shift_off, op.act, (bf16*)dst, st);
+                              f32 + op.scale_off, f32 + op.shift_off, op.act, (bf16*)dst, n_cu, st);
         kind = KC_DIRECT;
         fl = conv_flops(op, batch);
         by = conv_bytes(op, batch);
