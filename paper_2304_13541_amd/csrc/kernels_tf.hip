@@ -8,13 +8,21 @@
 // values stay in registers, mean and (biased) variance are fp32 block
 // reductions (wave shuffles, then one LDS value per wave), output bf16.
 //
-// Attention: one block per (head, sequence).  Queries, keys and values of
-// the sequence's T <= 48 tokens (64 dims per head) are read from the fused
-// q|k|v projection [tokens][3 * width] into LDS as fp32; the T x T scores
-// q_i . k_j / 8 are formed in LDS, each row is turned into softmax weights
-// by one wave (max, exp, sum), and the outputs o_i = sum_j p_ij v_j are
-// written as bf16 at the head's columns of [tokens][width].  The sequence is
-// short (tens of tokens), so this is plain fp32 vector arithmetic.
+// Attention: one block per (head, sequence), one wave per 16 queries of the
+// sequence's T <= 48 tokens (64 dims per head), everything in registers on the
+// matrix cores.  Scores as S^T = K Q^T (v_mfma_f32_16x16x32_bf16: bf16
+// products, fp32 sums): a lane then holds four keys 4 * (lane / 16) + i of
+// each 16-key tile for the query lane % 16, the softmax is a reduction over
+// its own values and the four lanes of that query, and the fp32 weights are
+// already the B operand of O^T = V^T P^T on v_mfma_f32_16x16x4_f32 (step i of
+// a tile takes key 4 * quad + i; the sum over keys has no order to keep).  The
+// weights so stay fp32.  Row m of dim tile t is dim 4 m + t: a lane reads four
+// consecutive dims of a key (8 bytes) and ends with 16 consecutive dims of
+// its query, two 16-byte stores.  All of a wave's loads are issued at its
+// start: the kernel is bound by that one latency and the launch.  Measured on
+// MI355X, 16 sequences of 20 tokens, 12 heads: 3.3 us against 8.6 for the same sums
+// as fp32 vector arithmetic from LDS (three barriers, scalar loads); 32
+// sequences of 48 tokens 28.3 -> 6.1 us.
 #include "common.hpp"
 
 namespace dstack {
@@ -23,7 +31,7 @@ namespace {
 
 constexpr int LN_MAX_PER_THREAD = 8;  // rows of up to 2048 values
 constexpr int ATT_DH = 64;            // head width
-constexpr int ATT_MAX_T = 48;         // tokens per sequence (the four arrays fit 64 KB of LDS)
+constexpr int ATT_MAX_T = 48;         // tokens per sequence
 
 __device__ __forceinline__ float wave_sum(float v) {
 #pragma unroll
@@ -101,44 +109,104 @@ __global__ __launch_bounds__(256) void layernorm_kernel(const bf16* __restrict__
   ln_row(v, H, gamma, beta, eps, y + row * H, red);
 }
 
-__global__ __launch_bounds__(256) void attention_kernel(const bf16* __restrict__ qkv, int T, int width,
-                                                        bf16* __restrict__ out) {
-  __shared__ float q[ATT_MAX_T][ATT_DH + 1], k[ATT_MAX_T][ATT_DH + 1], v[ATT_MAX_T][ATT_DH + 1];
-  __shared__ float p[ATT_MAX_T][ATT_MAX_T + 1];
-  const int h = blockIdx.x, b = blockIdx.y, tid = threadIdx.x;
-  const long tok0 = (long)b * T;
-  for (int i = tid; i < T * ATT_DH; i += 256) {
-    const int r = i / ATT_DH, e = i - r * ATT_DH;
-    const bf16* src = qkv + (tok0 + r) * 3 * width + h * ATT_DH + e;
-    q[r][e] = (float)src[0];
-    k[r][e] = (float)src[width];
-    v[r][e] = (float)src[2 * width];
+// N consecutive bf16 values; one load where the tensor is 16-byte aligned
+template <int N, bool ALIGNED, typename V>
+__device__ __forceinline__ V load_bf16(const bf16* p) {
+  V v;
+  if (ALIGNED) {
+    v = *reinterpret_cast<const V*>(p);
+  } else {
+#pragma unroll
+    for (int i = 0; i < N; ++i) v[i] = p[i];
   }
-  __syncthreads();
-  const float scale = 0.125f;  // 1 / sqrt(64)
-  for (int i = tid; i < T * T; i += 256) {
-    const int r = i / T, c = i - r * T;
-    float d = 0.f;
-#pragma unroll 16
-    for (int e = 0; e < ATT_DH; ++e) d += q[r][e] * k[c][e];
-    p[r][c] = d * scale;
+  return v;
+}
+
+// NT = ceil(T / 16) waves and key tiles
+template <int NT, bool ALIGNED>
+__global__ __launch_bounds__(64 * NT) void attention_kernel(const bf16* __restrict__ qkv, int T, int width,
+                                                            bf16* __restrict__ out) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, col = lane & 15, quad = lane >> 4;
+  const long tok0 = (long)blockIdx.y * T;
+  const bf16* base = qkv + tok0 * 3 * width + blockIdx.x * ATT_DH;
+  const int query = wave * 16 + col;
+  bf16x8 qf[2], kf[NT][2];
+  bf16x4 vf[NT][4];
+  auto row = [&](int t) { return base + (long)min(t, T - 1) * 3 * width; };  // rows past T are masked below
+#pragma unroll
+  for (int s = 0; s < 2; ++s) qf[s] = load_bf16<8, ALIGNED, bf16x8>(row(query) + s * 32 + quad * 8);
+#pragma unroll
+  for (int kt = 0; kt < NT; ++kt)
+#pragma unroll
+    for (int s = 0; s < 2; ++s)
+      kf[kt][s] = load_bf16<8, ALIGNED, bf16x8>(row(kt * 16 + col) + width + s * 32 + quad * 8);
+#pragma unroll
+  for (int kt = 0; kt < NT; ++kt)
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      vf[kt][i] = load_bf16<4, ALIGNED, bf16x4>(row(kt * 16 + 4 * quad + i) + 2 * width + 4 * col);
+
+  f32x4 p[NT];
+  float mx = -INFINITY;
+#pragma unroll
+  for (int kt = 0; kt < NT; ++kt) {
+    p[kt] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int s = 0; s < 2; ++s) p[kt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[kt][s], qf[s], p[kt], 0, 0, 0);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      p[kt][i] *= 0.125f;  // 1 / sqrt(64)
+      if (kt * 16 + 4 * quad + i < T) mx = fmaxf(mx, p[kt][i]);
+    }
   }
-  __syncthreads();
-  const int lane = tid & 63, wave = tid >> 6;
-  for (int r = wave; r < T; r += 4) {  // one wave per row: lane j holds key j
-    const float s = lane < T ? p[r][lane] : -INFINITY;
-    const float mx = wave_max(s);
-    const float ex = lane < T ? __expf(s - mx) : 0.f;
-    const float sum = wave_sum(ex);
-    if (lane < T) p[r][lane] = ex / sum;
+  mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
+  mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+  float sum = 0.f;
+#pragma unroll
+  for (int kt = 0; kt < NT; ++kt)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      p[kt][i] = kt * 16 + 4 * quad + i < T ? __expf(p[kt][i] - mx) : 0.f;
+      sum += p[kt][i];
+    }
+  sum += __shfl_xor(sum, 16, 64);
+  sum += __shfl_xor(sum, 32, 64);
+  f32x4 o[4];
+#pragma unroll
+  for (int t = 0; t < 4; ++t) o[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int kt = 0; kt < NT; ++kt)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const bool live = kt * 16 + 4 * quad + i < T;
+      const float w = p[kt][i] / sum;
+#pragma unroll
+      for (int t = 0; t < 4; ++t)
+        o[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(live ? (float)vf[kt][i][t] : 0.f, w, o[t], 0, 0, 0);
+    }
+  if (query >= T) return;
+  bf16* dst = out + (tok0 + query) * width + blockIdx.x * ATT_DH + 16 * quad;  // dim 16 * quad + 4 i + t
+#pragma unroll
+  for (int u = 0; u < 2; ++u) {
+    bf16x8 r;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) r[j] = (bf16)o[j & 3][2 * u + (j >> 2)];
+    if (ALIGNED) {
+      *reinterpret_cast<bf16x8*>(dst + 8 * u) = r;
+    } else {
+#pragma unroll
+      for (int j = 0; j < 8; ++j) dst[8 * u + j] = r[j];
+    }
   }
-  __syncthreads();
-  for (int i = tid; i < T * ATT_DH; i += 256) {
-    const int r = i / ATT_DH, e = i - r * ATT_DH;
-    float o = 0.f;
-    for (int j = 0; j < T; ++j) o += p[r][j] * v[j][e];
-    out[(tok0 + r) * width + h * ATT_DH + e] = (bf16)o;
-  }
+}
+
+template <int NT>
+void attention_launch(const bf16* qkv, int B, int T, int heads, bf16* out, hipStream_t st) {
+  const dim3 grid((unsigned)heads, (unsigned)B);
+  if ((((uintptr_t)qkv | (uintptr_t)out) & 15) == 0)  // rows are multiples of 128 bytes
+    launch(attention_kernel<NT, true>, grid, dim3(64 * NT), 0, st, qkv, T, heads * ATT_DH, out);
+  else
+    launch(attention_kernel<NT, false>, grid, dim3(64 * NT), 0, st, qkv, T, heads * ATT_DH, out);
 }
 
 }  // namespace
@@ -169,7 +237,12 @@ dstack_status launch_attention(const bf16* qkv, int B, int T, int heads, int dh,
   DS_CHECK(B > 0 && T > 0 && heads > 0, DSTACK_E_INVALID, "attention: bad shape");
   DS_CHECK(dh == ATT_DH && T <= ATT_MAX_T && heads <= 65535 && B <= 65535, DSTACK_E_UNSUPPORTED,
            "attention: head width 64 and at most 48 tokens");
-  launch(attention_kernel, dim3((unsigned)heads, (unsigned)B), dim3(256), 0, st, qkv, T, heads * dh, out);
+  if (T <= 16)
+    attention_launch<1>(qkv, B, T, heads, out, st);
+  else if (T <= 32)
+    attention_launch<2>(qkv, B, T, heads, out, st);
+  else
+    attention_launch<3>(qkv, B, T, heads, out, st);
   DS_HIP(hipGetLastError());
   return DSTACK_OK;
 }
