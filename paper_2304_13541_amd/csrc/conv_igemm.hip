@@ -22,7 +22,8 @@
 // (row/2) % 8, so the 16 rows an MFMA fragment read touches fall on 16
 // distinct 4-bank groups.
 //
-// Compute.  256 threads = 4 waves in a WN x WM grid over the (BN x BM) tile;
+// Compute.  KG groups of 256 threads = 4 waves in a WN x WM grid over the
+// (BN x BM) tile;
 // each wave issues v_mfma_f32_16x16x32_bf16 on its (BN/WN x BM/WM) sub-tile.
 // Operand layouts (checked on the device): lane l holds A[l%16][8*(l/16)..+8)
 // and B[8*(l/16)..+8)[l%16]; the result holds C[4*(l/16)+i][l%16], i = 0..3,
@@ -65,8 +66,8 @@ struct ConvArgs {
 // the general per-chunk (r, s, c) decomposition.
 enum ConvMode { MODE_1X1 = 0, MODE_TILED = 1, MODE_GENERIC = 2, MODE_1X1S1 = 3 };
 
-template <int BN, int BM, int WN, int WM, int STAGES, int MODE, bool OUT_F32, bool SPLIT>
-__global__ __launch_bounds__(256) void conv_igemm_kernel(ConvArgs a) {
+template <int BN, int BM, int WN, int WM, int STAGES, int MODE, bool OUT_F32, bool SPLIT, int KG>
+__global__ __launch_bounds__(256 * KG) void conv_igemm_kernel(ConvArgs a) {
   constexpr int ROWS = BN + BM;
   constexpr int STAGE_BYTES = ROWS * ROW_BYTES;
   constexpr int LPW = ROWS / 32;        // wave-loads (8 rows each) per wave per stage
@@ -75,11 +76,12 @@ __global__ __launch_bounds__(256) void conv_igemm_kernel(ConvArgs a) {
   static_assert(BN % 32 == 0 && BM % 32 == 0 && WN * WM == 4 && TN >= 1 && TM >= 1, "tile shape");
   static_assert(STAGES >= 2 && STAGES <= 4, "2..4 stages");
 
-  __shared__ __attribute__((aligned(1024))) unsigned char lds[STAGES * STAGE_BYTES];
+  __shared__ __attribute__((aligned(1024))) unsigned char lds[KG * STAGES * STAGE_BYTES];
 
   const int tid = threadIdx.x;
   const int lane = tid & 63;
-  const int wave = tid >> 6;
+  const int wave = KG == 1 ? tid >> 6 : (tid >> 6) & 3;                   // within its depth group
+  const int kg = KG == 1 ? 0 : __builtin_amdgcn_readfirstlane(tid >> 8);  // depth group
   const int wn = wave % WN, wm = wave / WN;
   // XCD-aware tile order: consecutive workgroups go round-robin to the 8 XCDs,
   // so XCD x is given the contiguous tile range [x*q + min(x, r), ...) of the
@@ -99,7 +101,8 @@ __global__ __launch_bounds__(256) void conv_igemm_kernel(ConvArgs a) {
   const i32x4 wrs = make_rsrc(a.w, (unsigned)((long)a.K * a.Kg * 2));
   const i32x4 xrs = make_rsrc(a.x, (unsigned)((long)a.N * a.H * a.W * a.C * 2));
   const int wave_u = __builtin_amdgcn_readfirstlane(wave);  // wave-uniform copy: scalar branches
-  const unsigned lds0 = __builtin_amdgcn_readfirstlane(lds_address(lds));
+  unsigned char* const ring = lds + kg * STAGES * STAGE_BYTES;  // the depth group's ring
+  const unsigned lds0 = __builtin_amdgcn_readfirstlane(lds_address(ring));
 
   // ---- per-lane addressing ----
   // Every wave moves WPW 8-row groups of weight rows and APW 8-row groups of
@@ -231,7 +234,7 @@ __global__ __launch_bounds__(256) void conv_igemm_kernel(ConvArgs a) {
   // scale and shift are fetched now and its residual rows right after the
   // last depth tile's loads, so that neither round trip follows the loop.
   constexpr int G = BN / 4;
-  constexpr int RSTEP = 256 / G;
+  constexpr int RSTEP = 256 * KG / G;
   constexpr int ROWS_PT = BM / RSTEP;
   static_assert(256 % G == 0 && BM % RSTEP == 0, "epilogue thread mapping");
   static_assert(2 * LPW + ROWS_PT < 64, "vmcnt range");
@@ -264,15 +267,16 @@ __global__ __launch_bounds__(256) void conv_igemm_kernel(ConvArgs a) {
   // prologue: STAGES-1 tiles in flight
 #pragma unroll
   for (int s = 0; s < STAGES - 1; ++s)
-    if (kt0 + s < kt1) issue(kt0 + s, s);
-  if (has_res && kt1 - kt0 <= STAGES - 1) load_res();
+    if (kt0 + kg + s * KG < kt1) issue(kt0 + kg + s * KG, s);
+  if (has_res && kt1 - kt0 - kg <= (STAGES - 1) * KG) load_res();
 
-  for (int kt = kt0; kt < kt1; ++kt) {
-    const int st = (kt - kt0) % STAGES;
+  // depth group kg takes every KG-th tile from kt0 + kg; both groups pass every barrier
+  for (int kt = kt0 + kg; kt - kg < kt1; kt += KG) {
+    const int st = (kt - kt0) / KG % STAGES;
     // tiles issued after kt that may stay in flight
     // (the residual rows, once issued, are the youngest loads)
-    const int after = min(STAGES - 2, kt1 - 1 - kt);
-    if (has_res && kt1 - 1 - kt <= STAGES - 2) {
+    const int after = min(STAGES - 2, (kt1 - 1 - kt) / KG);
+    if (has_res && (kt1 - 1 - kt) / KG <= STAGES - 2) {
       if (after >= 2)
         wait_vmcnt<2 * LPW + ROWS_PT>();
       else if (after == 1)
@@ -287,12 +291,13 @@ __global__ __launch_bounds__(256) void conv_igemm_kernel(ConvArgs a) {
       else
         wait_vmcnt<0>();
     }
-    __syncthreads();  // every wave's part of tile kt is in LDS; every wave is done with tile kt-1
-    if (kt + STAGES - 1 < kt1) {
-      issue(kt + STAGES - 1, (kt - kt0 + STAGES - 1) % STAGES);
-      if (has_res && kt + STAGES - 1 == kt1 - 1) load_res();
+    __syncthreads();  // every wave's part of the step's tiles is in LDS; every wave is done with the last step's
+    if (kt + (STAGES - 1) * KG < kt1) {
+      issue(kt + (STAGES - 1) * KG, ((kt - kt0) / KG + STAGES - 1) % STAGES);
+      if (has_res && (KG == 1 ? kt + STAGES == kt1 : kt + STAGES * KG >= kt1)) load_res();
     }
-    const unsigned char* sb = lds + st * STAGE_BYTES;
+    if (KG > 1 && kt >= kt1) break;  // an odd count: the last step has no tile for this group
+    const unsigned char* sb = ring + st * STAGE_BYTES;
 #pragma unroll
     for (int ks = 0; ks < BK / 8; ks += 4) {
       bf16x8 af[TN], bfr[TM];
@@ -314,11 +319,11 @@ __global__ __launch_bounds__(256) void conv_igemm_kernel(ConvArgs a) {
   // 16-byte units XOR-swizzled by pixel % 8), then consecutive threads take
   // consecutive 4-channel groups of a pixel row, so residual reads and output
   // writes cover whole row segments.
-  static_assert(BM * BN * 4 <= STAGES * STAGE_BYTES, "epilogue tile must fit in the stage ring");
+  static_assert(BM * BN * 4 <= STAGES * STAGE_BYTES, "each depth group's fp32 tile must fit in its ring");
   static_assert(BN / 4 >= 8, "swizzle needs 8 units per row");
   wait_vmcnt<0>();  // scale, shift and residual rows are in registers: no waits between the row stores
   __syncthreads();  // all waves are done reading the last stage
-  float* ct = reinterpret_cast<float*>(lds);
+  float* ct = reinterpret_cast<float*>(lds) + kg * BM * BN;
   auto cidx = [](int pl, int cl) { return pl * BN + ((((cl >> 2) ^ (pl & 7))) << 2); };
 #pragma unroll
   for (int i = 0; i < TN; ++i) {
@@ -333,7 +338,11 @@ __global__ __launch_bounds__(256) void conv_igemm_kernel(ConvArgs a) {
   // all of the thread's rows are read from LDS before the first store
   f32x4 t[ROWS_PT];
 #pragma unroll
-  for (int k = 0; k < ROWS_PT; ++k) t[k] = *reinterpret_cast<const f32x4*>(ct + cidx(pl0 + k * RSTEP, cl));
+  for (int k = 0; k < ROWS_PT; ++k) {
+    const float* src = reinterpret_cast<const float*>(lds) + cidx(pl0 + k * RSTEP, cl);
+    t[k] = *reinterpret_cast<const f32x4*>(src);
+    if (KG == 2) t[k] += *reinterpret_cast<const f32x4*>(src + BM * BN);
+  }
   if (SPLIT) {
     // Fused reduction: every block writes its slice with device-scope stores
     // (they pass the per-XCD L2s) and bumps the tile's counter once they have
@@ -620,6 +629,23 @@ constexpr int kShortSplitTiles = 3;
 static bool short_ring(int per, int splits, long blocks, int n_cu) {
   return per <= (splits > 1 ? kShortSplitTiles : kShortTiles) && blocks > 2L * n_cu;
 }
+// 64 x 64 and 32 x 128 tiles with at most one block per CU run as two depth groups of 4
+// waves, each with a ring of 4 tiles, that take the tiles in turn and add
+// their sums in the epilogue.  With one block of 4 waves on a CU a step is a
+// chain of barrier, LDS reads and 8 products (0.26 us for 0.05 us of
+// products, and a ring of 8 tiles does not shorten it: 6.7 -> 7.3 us); two
+// groups halve the number of steps.  Measured on 256 CUs, one group against
+// two: 320 x 3072 of depth 768 6.85 against 5.93 us, 20 x 768 of depth 768
+// 6.26 / 5.38, 4488 x 128 of depth 1024 7.74 / 6.59, slices of 6 tiles
+// 8.07 / 7.33, 1458 x 20 of depth 1224 (3x3) 13.8 / 9.6; slices of 4 tiles
+// 6.80 / 7.13, hence kGroupTiles.  The block's 128 or 160 KB of LDS leave no room for another on its CU, and workgroups go round
+// the shader engines, which hold different numbers of CUs when the partition
+// is no multiple of 32: blocks are counted against whole groups of 32.
+constexpr int kGroupTiles = 6;
+constexpr int LONG_RING = 8;
+static bool two_groups(int bn, int bm, int per, long blocks, int n_cu) {
+  return bn * bm == 64 * 64 && per >= kGroupTiles && blocks <= n_cu / 32 * 32;
+}
 static int short_blocks_per_cu(int bn, int bm, bool split) {
   const int ring = 2 * (bn + bm) * ROW_BYTES;
   const int regs = bn * bm >= 16384 ? (split ? 240 : 200) : bn * bm >= 8192 ? (split ? 144 : 128) : (split ? 112 : 80);
@@ -669,29 +695,33 @@ constexpr int conv_stages(int bn, int bm) {
   return s < 2 ? 2 : (s > 4 ? 4 : s);
 }
 
+template <int BN, int BM, int WN, int WM, int STAGES, int MODE, int KG>
+static void launch_ring(const ConvArgs& a, bool f32, int splits, hipStream_t st) {
+  const dim3 grid(a.tiles, 1, splits);
+  // with dispatch events armed: both on this kernel (the split-K reduction is in it)
+  const DispatchEvents& de = dispatch_events();
+  if (splits > 1)
+    launch_k(conv_igemm_kernel<BN, BM, WN, WM, STAGES, MODE, false, true, KG>, grid, 256 * KG, st, de.start, de.stop,
+             a);
+  else if (f32)
+    launch_k(conv_igemm_kernel<BN, BM, WN, WM, STAGES, MODE, true, false, KG>, grid, 256 * KG, st, de.start, de.stop,
+             a);
+  else
+    launch_k(conv_igemm_kernel<BN, BM, WN, WM, STAGES, MODE, false, false, KG>, grid, 256 * KG, st, de.start, de.stop,
+             a);
+}
+
 template <int BN, int BM, int WN, int WM, int MODE>
 static void launch_mode(ConvArgs a, bool f32, int splits, int stages, hipStream_t st) {
-  constexpr int STAGES = conv_stages(BN, BM);
   a.tiles_n = ceil_div(a.K, BN);
   a.tiles = ceil_div(a.M, BM) * a.tiles_n;
   a.div_tn = FastDiv::make(a.tiles_n);
-  dim3 grid(a.tiles, 1, splits);
-  // with dispatch events armed: both on this kernel (the split-K reduction is in it)
-  const DispatchEvents& de = dispatch_events();
-  hipEvent_t e0 = de.start, e1 = de.stop;
-  if (STAGES > 2 && stages == 2) {
-    if (splits > 1)
-      launch_k(conv_igemm_kernel<BN, BM, WN, WM, 2, MODE, false, true>, grid, 256, st, e0, e1, a);
-    else if (f32)
-      launch_k(conv_igemm_kernel<BN, BM, WN, WM, 2, MODE, true, false>, grid, 256, st, e0, e1, a);
-    else
-      launch_k(conv_igemm_kernel<BN, BM, WN, WM, 2, MODE, false, false>, grid, 256, st, e0, e1, a);
-  } else if (splits > 1)
-    launch_k(conv_igemm_kernel<BN, BM, WN, WM, STAGES, MODE, false, true>, grid, 256, st, e0, e1, a);
-  else if (f32)
-    launch_k(conv_igemm_kernel<BN, BM, WN, WM, STAGES, MODE, true, false>, grid, 256, st, e0, e1, a);
+  if constexpr (BN * BM == 64 * 64)
+    if (stages == LONG_RING) return launch_ring<BN, BM, WN, WM, LONG_RING / 2, MODE, 2>(a, f32, splits, st);
+  if (stages == 2)
+    launch_ring<BN, BM, WN, WM, 2, MODE, 1>(a, f32, splits, st);
   else
-    launch_k(conv_igemm_kernel<BN, BM, WN, WM, STAGES, MODE, false, false>, grid, 256, st, e0, e1, a);
+    launch_ring<BN, BM, WN, WM, conv_stages(BN, BM), MODE, 1>(a, f32, splits, st);
 }
 
 template <int BN, int BM, int WN, int WM>
@@ -788,6 +818,7 @@ static ConvLaunchPlan conv_launch_plan(const ConvArgs& a, bool out_fp32, bool ca
   const long tiles = (long)ceil_div(a.M, p.bm) * ceil_div(a.K, p.bn);
   L.stages = conv_stages(p.bn, p.bm);
   if (L.stages > 2 && short_ring(L.kt_per_split, L.splits, tiles * L.splits, a.n_cu)) L.stages = 2;
+  if (two_groups(p.bn, p.bm, L.kt_per_split, tiles * L.splits, a.n_cu)) L.stages = LONG_RING;
   return L;
 }
 
