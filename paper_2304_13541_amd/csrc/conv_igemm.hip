@@ -629,18 +629,19 @@ constexpr int kShortSplitTiles = 3;
 static bool short_ring(int per, int splits, long blocks, int n_cu) {
   return per <= (splits > 1 ? kShortSplitTiles : kShortTiles) && blocks > 2L * n_cu;
 }
-// 64 x 64 and 32 x 128 tiles with at most one block per CU run as two depth groups of 4
-// waves, each with a ring of 4 tiles, that take the tiles in turn and add
-// their sums in the epilogue.  With one block of 4 waves on a CU a step is a
-// chain of barrier, LDS reads and 8 products (0.26 us for 0.05 us of
-// products, and a ring of 8 tiles does not shorten it: 6.7 -> 7.3 us); two
+// 64 x 64 and 32 x 128 tiles with at most one block per CU run as two depth
+// groups of 4 waves, each with a ring of 4 tiles, that take the tiles in turn
+// and add their sums in the epilogue.  With one block of 4 waves on a CU a
+// step is a chain of barrier, LDS reads and 8 products (0.26 us for 0.05 us
+// of products, and a ring of 8 tiles does not shorten it: 6.7 -> 7.3 us); two
 // groups halve the number of steps.  Measured on 256 CUs, one group against
 // two: 320 x 3072 of depth 768 6.85 against 5.93 us, 20 x 768 of depth 768
 // 6.26 / 5.38, 4488 x 128 of depth 1024 7.74 / 6.59, slices of 6 tiles
 // 8.07 / 7.33, 1458 x 20 of depth 1224 (3x3) 13.8 / 9.6; slices of 4 tiles
-// 6.80 / 7.13, hence kGroupTiles.  The block's 128 or 160 KB of LDS leave no room for another on its CU, and workgroups go round
-// the shader engines, which hold different numbers of CUs when the partition
-// is no multiple of 32: blocks are counted against whole groups of 32.
+// 6.80 / 7.13, hence kGroupTiles.  The block's 128 or 160 KB of LDS leave no
+// room for another on its CU, and workgroups go round the shader engines,
+// which hold different numbers of CUs when the partition is no multiple of
+// 32: blocks are counted against whole groups of 32.
 constexpr int kGroupTiles = 6;
 constexpr int LONG_RING = 8;
 static bool two_groups(int bn, int bm, int per, long blocks, int n_cu) {
@@ -772,10 +773,17 @@ static dstack_status conv_shape(int N, int H, int W, int C, int K, int R, int S,
 // kernel's, which is about 15% low unsplit (estimate against measured less a
 // launch gap of 1.3 us: 11.5 / 12.1 to 15.2 / 19.7 us) and high for split
 // 64 x 64 tiles (10.9 / 7.6 to 14.0 / 11.4 us); the halo kernel's are within
-// 5%.  The general kernel keeps partitions of fewer than 64 CUs, fp32
-// outputs, and the shapes whose split plan needs more than 32 MiB of slices
-// (the allocation-free entry point refuses those).
-constexpr int kHaloMinCus = 64;
+// 5% (8% high on a small partition whose shader engines hold different
+// numbers of CUs, hence the margin).  The general kernel keeps fp32 outputs
+// and the shapes whose split plan needs more than 32 MiB of slices (the
+// allocation-free entry point refuses those).  Partitions of fewer than 32
+// CUs keep a split general plan, whose slices callers with the fixed scratch
+// count on there (24 CUs, 6 images of 7x7x448 -> 160: 15.9 us, 13.2 in this
+// kernel); unsplit plans go by the estimates on any number of CUs (general
+// against this kernel: 24 CUs, 8 images of 28x28x128 -> 128 30.9 / 25.5 us;
+// 32 CUs, 16 of 14x14x256 -> 256 32.8 / 26.8; 48 CUs, 2 of 57x55x512 -> 160
+// 106.7 / 74.0; 56 CUs, 4 of 14x14x256 -> 256 20.1 / 12.5).
+constexpr int kHaloSplitCus = 32;
 static double general_correction(const ConvPlan& p, const ConvArgs& a) {
   if (p.splits > 1) return p.bn * p.bm <= 64 * 64 ? 0.75 : 1.0;
   // over many rounds the two blocks of a CU drift apart and overlap
@@ -800,9 +808,10 @@ static ConvLaunchPlan conv_launch_plan(const ConvArgs& a, bool out_fp32, bool ca
   L.mode = one ? (a.stride == 1 ? MODE_1X1S1 : MODE_1X1) : (a.C % BK == 0 && a.R * a.S <= 32 ? MODE_TILED : MODE_GENERIC);
   const ConvPlan p = choose_plan(a.M, a.K, a.Kg, a.n_cu, can_split && !out_fp32, split_bytes);
   if (halo && a.R == 3 && a.S == 3 && a.stride == 1 && a.pad == 1 && a.C % BK == 0 && a.K % 8 == 0 && !out_fp32 &&
-      a.n_cu >= kHaloMinCus && (p.splits == 1 || (size_t)p.splits * a.M * a.K * sizeof(float) <= ((size_t)32 << 20)) &&
+      (p.splits == 1 ||
+       (a.n_cu >= kHaloSplitCus && (size_t)p.splits * a.M * a.K * sizeof(float) <= ((size_t)32 << 20))) &&
       halo_plan(a.N, a.H, a.W, a.C, a.K, a.n_cu, can_split, split_bytes, halo) &&
-      halo->cost < general_correction(p, a) * p.cost) {
+      halo->cost * (a.n_cu < 64 && a.n_cu % 32 ? 1.08 : 1.0) < general_correction(p, a) * p.cost) {
     L.kernel = 2;
     L.mode = MODE_TILED;
     halo_tile(*halo, &L.bn, &L.bm, &L.stages);

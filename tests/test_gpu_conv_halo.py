@@ -37,13 +37,15 @@ def plan(ds, N, H, W, C, K, act, n_cu, **kw):
 
 def test_dispatch_rule():
     """Only 3x3, stride 1, pad 1, whole 64-channel chunks, K % 8 == 0, bf16
-    output and 64 or more CUs take the kernel; its splits need the workspace."""
+    output take the kernel, on fewer than 32 CUs only where the general plan does
+    not split; its splits need the workspace."""
     import paper_2304_13541_amd as ds
-    assert plan(ds, 16, 14, 14, 256, 256, 1, 128)["kernel"] == 2
+    assert all(plan(ds, 16, 14, 14, 256, 256, 1, n)["kernel"] == 2 for n in (24, 32, 56, 128))
+    assert plan(ds, 2, 9, 9, 256, 384, 1, 24)["kernel"] == 0 and plan(ds, 2, 9, 9, 256, 384, 1, 32)["kernel"] == 2
     for C, K, R, st, pad, f32, n_cu in [(256, 256, 3, 2, 1, False, 128), (256, 256, 3, 1, 0, False, 128),
                                         (256, 256, 5, 1, 2, False, 128), (256, 256, 1, 1, 0, False, 128),
                                         (264, 256, 3, 1, 1, False, 128), (256, 252, 3, 1, 1, False, 128),
-                                        (256, 256, 3, 1, 1, True, 128), (256, 256, 3, 1, 1, False, 56)]:
+                                        (256, 256, 3, 1, 1, True, 128)]:
         p = ds.conv2d_plan(16, 14, 14, C, K, R, R, st, pad, 1, f32, n_cu)
         assert p["kernel"] == 0, (C, K, R, st, pad, f32, n_cu, p)
     rng = np.random.default_rng(3)
