@@ -122,6 +122,17 @@ __device__ __forceinline__ float apply_act(float v, int act) {
   return v;
 }
 
+// One LSTM cell from its gates (i, f, g, o): the new cell state and h.  Every
+// path of the recurrence computes its cells here.
+__device__ __forceinline__ void lstm_cell(const float (&g)[4], float& c, float& h) {
+  const float ig = 1.f / (1.f + __expf(-g[0]));
+  const float fg = 1.f / (1.f + __expf(-g[1]));
+  const float gt = tanhf(g[2]);
+  const float og = 1.f / (1.f + __expf(-g[3]));
+  c = fg * c + ig * gt;
+  h = og * tanhf(c);
+}
+
 // split-K arrival counters per model workspace (conv tiles of one launch)
 constexpr int SPLITK_TILE_COUNTERS = 4096;
 

@@ -286,12 +286,8 @@ __global__ __launch_bounds__(256) void lstm_step_kernel(const float* __restrict_
       const int r = g * 4 + cu;
       g4[g] = gs[0][mt][u][r][bc] + gs[1][mt][u][r][bc] + gs[2][mt][u][r][bc] + gs[3][mt][u][r][bc] + gxv[q][g];
     }
-    const float ig = 1.f / (1.f + __expf(-g4[0]));
-    const float fg = 1.f / (1.f + __expf(-g4[1]));
-    const float gt = tanhf(g4[2]);
-    const float og = 1.f / (1.f + __expf(-g4[3]));
-    const float cn = fg * cprev[q] + ig * gt;
-    const float hn = og * tanhf(cn);
+    float cn = cprev[q], hn;
+    lstm_cell(g4, cn, hn);
     c[(long)cb * H + cj] = cn;
     const bf16 hb = (bf16)hn;
     hnext[(long)cb * H + cj] = hb;

@@ -53,22 +53,7 @@ struct LstmSeqArgs {
   long limit;        // ticks (10 ns) a wait may last
 };
 
-__device__ __forceinline__ float lstm_sigmoid(float v) { return __builtin_amdgcn_rcpf(1.f + __expf(-v)); }
-// tanh: its series to x^9 below 1/4 (the next term is 1e-8 of it), else 1 - 2 / (1 + e^2|x|)
-__device__ __forceinline__ float lstm_tanh(float v) {
-  const float x = fabsf(v), q = v * v;
-  const float s = v + v * q * (-1.f / 3 + q * (2.f / 15 + q * (-17.f / 315 + q * (62.f / 2835))));
-  const float e = copysignf(1.f - 2.f * __builtin_amdgcn_rcpf(1.f + __expf(2.f * x)), v);
-  return x < 0.25f ? s : e;
-}
-
 __device__ __forceinline__ unsigned bf16_bits(bf16 v) { return (unsigned)__builtin_bit_cast(unsigned short, v); }
-
-__device__ __forceinline__ void lstm_cell(const f32x4& g, float& c, float& h) {
-  const float ig = lstm_sigmoid(g[0]), fg = lstm_sigmoid(g[1]), gt = lstm_tanh(g[2]), og = lstm_sigmoid(g[3]);
-  c = fg * c + ig * gt;
-  h = og * lstm_tanh(c);
-}
 
 // The whole recurrence by one block, without waiting for any other (a wave
 // takes row tiles wave, wave + 8, ...; loads of 8 depth steps in flight).
@@ -95,7 +80,7 @@ __device__ void lstm_serial(const LstmSeqArgs& a) {
             for (int s = 0; s < 8; ++s) acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wv[s], hv[s], acc, 0, 0, 0);
           }
         // lane (quad g, column b) holds gate g of units 0..3; gather the four gates of unit `quad`
-        f32x4 g4;
+        float g4[4];
 #pragma unroll
         for (int g = 0; g < 4; ++g) {
           float v = 0.f;
@@ -244,12 +229,14 @@ __global__ __launch_bounds__(LS_THREADS, RT <= 4 && RT * KSW <= 8 ? 4 : 2) void 
     }
     __syncthreads();
     const int flag = *(volatile int*)&flags[t3];
-    f32x4 g4 = {gxv[0], gxv[1], gxv[2], gxv[3]};
+    float g4[4] = {gxv[0], gxv[1], gxv[2], gxv[3]};
     if (t > 0 && wave * 64 < CELLS) {
       f32x4 v[LS_WAVES];
 #pragma unroll
       for (int k = 0; k < LS_WAVES; ++k) v[k] = *reinterpret_cast<const f32x4*>(rb + k * RT * TS + cl);
-      g4 += ((v[0] + v[1]) + (v[2] + v[3])) + ((v[4] + v[5]) + (v[6] + v[7]));
+      const f32x4 sum = ((v[0] + v[1]) + (v[2] + v[3])) + ((v[4] + v[5]) + (v[6] + v[7]));
+#pragma unroll
+      for (int g = 0; g < 4; ++g) g4[g] += sum[g];
     }
     if (flag >> 16) break;  // block-uniform: written before the barrier
     // read by all before this step's barrier, set again after the next one's

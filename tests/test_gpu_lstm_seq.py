@@ -145,3 +145,25 @@ def test_replays_equal_eager(env):
         g.replay()
         hb, hf = layer.result()
         assert np.array_equal(hb, want[0]) and np.array_equal(hf, want[1])
+
+
+def test_cells_are_those_of_the_step_path(env):
+    """Without a recurrent product there is no sum to order: the one launch (4 steps) and the step path (3 steps)
+    give the same bits.  Gates over the sigmoids' and tanh's ranges, the tanh gates densest around 1/4."""
+    ds, gu, inputs, oracle, torch = env
+    B, I, H = 3, 8, 1024
+    rng = np.random.default_rng(41)
+    bias = rng.uniform(-6, 6, 4 * H).astype(np.float32)
+    bias[2 * H:3 * H] = np.concatenate([rng.uniform(-4, 4, H // 2), rng.uniform(0.2, 0.35, H // 2)])
+    bias[:H // 4] = bias[3 * H:3 * H + H // 4] = 30.0  # open input and output gates: h = tanh(c)
+    x, wih, whh = (gu.dev_bf16(np.zeros(s, np.uint16)) for s in ((4, B, I), (4 * H, I), (4 * H, H)))
+    out = []
+    for T in (3, 4):
+        hb, hf = gu.empty_bf16((T, B, H)), gu.empty_f32((T, B, H))
+        ws = torch.empty(ds.lstm_workspace_bytes(T, B, H), dtype=torch.uint8, device="cuda:0")
+        ds.lstm_layer(x[:T], wih, whh, gu.dev_f32(bias), hb, hf, ws)
+        torch.cuda.synchronize()
+        out.append(hf.cpu().numpy()[:3])
+    diff = np.abs(out[0].view(np.int32).astype(np.int64) - out[1].view(np.int32))
+    print("  differing values", int((diff > 0).sum()), "largest distance, ulp", int(diff.max()), flush=True)
+    assert np.array_equal(out[0], out[1])
