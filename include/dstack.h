@@ -755,6 +755,12 @@ dstack_status dstack_op_avgpool(const void* x, int N, int H, int W, int C, void*
 size_t dstack_lstm_workspace_bytes(int T, int B, int H);
 dstack_status dstack_op_lstm_layer(const void* x, int T, int B, int I, int H, const void* w_ih, const void* w_hh,
                                    const float* bias, void* h_bf16, float* h_f32, void* workspace, void* stream);
+/* The launch of an LSTM layer's recurrence (host only): row tiles of W_hh per
+ * workgroup and workgroups of the one launch, 0 and 0 where it takes one
+ * launch per step.  cu_mask: the stream's CU mask (8 words), NULL: the first
+ * n_cu CUs.  Masks that hold a part of an 8-CU slot take one launch per step. */
+dstack_status dstack_lstm_plan(int T, int B, int H, int n_cu, const uint32_t* cu_mask, int* row_tiles,
+                               int* workgroups);
 dstack_status dstack_op_lstm_layer_wait(const void* x, int T, int B, int I, int H, const void* w_ih,
                                         const void* w_hh, const float* bias, void* h_bf16, float* h_f32,
                                         void* workspace, int wait_us, void* stream);

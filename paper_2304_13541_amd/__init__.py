@@ -212,6 +212,7 @@ _SIGS = {
     "dstack_op_embed_ln": ([_vp, _i, _i, _i, _vp, _vp, _vp, _i, _vp, _vp, ctypes.c_float, _vp, _vp], _i),
     "dstack_op_layernorm": ([_vp, _i, _i, _vp, _vp, ctypes.c_float, _vp, _vp], _i),
     "dstack_op_attention": ([_vp, _i, _i, _i, _i, _vp, _vp], _i),
+    "dstack_lstm_plan": ([_i, _i, _i, _i, _vp, _vp, _vp], _i),
     "dstack_op_lstm_layer_wait": ([_vp, _i, _i, _i, _i, _vp, _vp, _vp, _vp, _vp, _vp, _i, _vp], _i),
     "dstack_op_lstm_layer": ([_vp, _i, _i, _i, _i, _vp, _vp, _vp, _vp, _vp, _vp, _vp], _i),
 }
@@ -693,6 +694,17 @@ def avgpool(x, y, stream=None):
 
 def lstm_workspace_bytes(T, B, H):
     return lib().dstack_lstm_workspace_bytes(T, B, H)
+
+
+def lstm_plan(T, B, H, n_cu=256, cu_mask=None):
+    """(row tiles, workgroups) of the recurrence's one launch, (0, 0): one launch per step (host only); cu_mask: the
+    stream's CU mask as an int (bit i: CU i), None: the first n_cu CUs."""
+    words = None
+    if cu_mask is not None:
+        words = (ctypes.c_uint32 * 8)(*((cu_mask >> (32 * i)) & 0xffffffff for i in range(8)))
+    rt, blocks = ctypes.c_int(), ctypes.c_int()
+    _check(lib().dstack_lstm_plan(T, B, H, n_cu, words, ctypes.byref(rt), ctypes.byref(blocks)))
+    return rt.value, blocks.value
 
 
 def lstm_layer(x, w_ih, w_hh, bias, h_bf16, h_f32, workspace, stream=None, wait_us=None):

@@ -1016,6 +1016,20 @@ size_t dstack_lstm_workspace_bytes(int T, int B, int H) {
          (size_t)2 * B * H * 2;
 }
 
+dstack_status dstack_lstm_plan(int T, int B, int H, int n_cu, const uint32_t* cu_mask, int* row_tiles,
+                               int* workgroups) {
+  return guarded([&] {
+    DS_CHECK(row_tiles && workgroups, DSTACK_E_INVALID, "lstm_plan: null pointer");
+    DS_CHECK(T >= 1 && B >= 1 && B <= 32 && H >= 32 && H % 32 == 0 && H <= 2048 && n_cu >= 0, DSTACK_E_UNSUPPORTED,
+             "lstm_plan: T >= 1, batch 1..32, H a multiple of 32, <= 2048");
+    LstmSeqPlan p{0, 0, 0};
+    if (!lstm_seq_plan(T, B, H, n_cu, cu_mask, &p)) p = LstmSeqPlan{0, 0, 0};
+    *row_tiles = p.row_tiles;
+    *workgroups = p.blocks;
+    return DSTACK_OK;
+  });
+}
+
 dstack_status dstack_op_lstm_layer_wait(const void* x, int T, int B, int I, int H, const void* w_ih, const void* w_hh,
                                         const float* bias, void* h_bf16, float* h_f32, void* workspace, int wait_us,
                                         void* stream) {

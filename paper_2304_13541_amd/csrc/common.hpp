@@ -192,10 +192,12 @@ dstack_status launch_lstm_step(const float* gx_t, const bf16* wp, const bf16* hp
 int lstm_units_per_block(int B, int H, int n_cu);
 // The recurrence of a whole sequence in one launch (plus one that clears its
 // exchange buffers): `groups` batch slices, row_tiles row tiles of W_hh per
-// block.  false: this shape on these CUs takes one launch per step.
+// block.  false: this shape on these CUs takes one launch per step.  mask: a
+// stream's CU mask (8 words), null: n_cu consecutive CUs.
 struct LstmSeqPlan {
   int groups, row_tiles, blocks;
 };
+bool lstm_seq_plan(int T, int B, int H, int n_cu, const uint32_t* mask, LstmSeqPlan* out);
 bool lstm_seq_plan(int T, int B, int H, int n_cu, hipStream_t st, LstmSeqPlan* out);
 size_t lstm_seq_exchange_bytes(int B, int H, const LstmSeqPlan& p);  // <= 4 (B + 1) H
 // whh row-major; c: [B][H] scratch; ctl: two words; limit: how long a block

@@ -303,25 +303,20 @@ static void lstm_seq_rt(const LstmSeqArgs& a, int rt, hipStream_t st) {
   }
 }
 
-// Blocks (one per CU) that a stream's CUs hold at once.  Blocks go round
-// robin to the XCDs and, in each, to the shader engines that have CUs in the
-// mask (slot j is on engine j % 4), whichever engine still has room: with
-// engines of unequal size the smallest fills first and holds the others up
-// (10 blocks per XCD on engines of 3, 3, 2 and 2 CUs took two rounds).
-static int lstm_seq_blocks(int n_cu, hipStream_t st) {
+// Blocks (one per CU) that CUs hold at once: `mask` is a stream's CU mask of
+// 256 bits, byte j the CUs of slot j, one on each XCD; null: the first n_cu / 8
+// slots.  Blocks go round robin to the XCDs and, in each, to the shader
+// engines that have CUs in the mask (slot j is on engine j % 4), whichever
+// engine still has room: with engines of unequal size the smallest fills first
+// and holds the others up (10 blocks per XCD on engines of 3, 3, 2 and 2 CUs
+// took two rounds).  A mask with a part of a slot gives the XCDs different
+// engines, which this does not count: no room.
+static int lstm_seq_blocks(int n_cu, const uint32_t* mask) {
   int per[4] = {0, 0, 0, 0};
-  uint32_t words[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-  int bits = 0;
-  if (st && hipExtStreamGetCUMask(st, 8, words) == hipSuccess) {
-    for (uint32_t w : words) bits += __builtin_popcount(w);
-  } else {
-    (void)hipGetLastError();
-  }
-  if (st && bits == n_cu) {  // (a launch planned for other CUs than the stream's: as for consecutive slots)
-    for (int slot = 0; slot < 32; ++slot)
-      if ((words[slot / 4] >> (8 * (slot % 4))) & 0xffu) ++per[slot % 4];
-  } else {
-    for (int slot = 0; slot < n_cu / 8; ++slot) ++per[slot % 4];
+  for (int slot = 0; slot < 32; ++slot) {
+    const uint32_t cus = mask ? (mask[slot / 4] >> (8 * (slot % 4))) & 0xffu : slot < n_cu / 8 ? 0xffu : 0u;
+    if (cus != 0 && cus != 0xffu) return 0;
+    if (cus) ++per[slot % 4];
   }
   int least = 0, engines = 0;
   for (int c : per)
@@ -338,13 +333,13 @@ static int lstm_seq_blocks(int n_cu, hipStream_t st) {
 // items (one MFMA column tile).  A block's weights must fit its registers:
 // RT * (depth steps per wave) <= 32.  Sequences of fewer than 4 steps and
 // partitions that cannot hold a group stay with one launch per step.
-bool lstm_seq_plan(int T, int B, int H, int n_cu, hipStream_t st, LstmSeqPlan* out) {
+bool lstm_seq_plan(int T, int B, int H, int n_cu, const uint32_t* mask, LstmSeqPlan* out) {
   if (T < 4) return false;
   const int tiles = H / 4, groups = (B + 15) / 16;
   int ksw = 1;
   while (ksw * LS_WAVES * 32 < H) ksw *= 2;
   if (ksw > 8) return false;
-  const int room = lstm_seq_blocks(n_cu, st);
+  const int room = lstm_seq_blocks(n_cu, mask);
   for (int rt = 2; rt <= (ksw == 8 ? 2 : 8); rt *= 2) {
     const int blocks = groups * ((tiles + rt - 1) / rt);
     if (blocks > room) continue;
@@ -352,6 +347,17 @@ bool lstm_seq_plan(int T, int B, int H, int n_cu, hipStream_t st, LstmSeqPlan* o
     return true;
   }
   return false;
+}
+
+bool lstm_seq_plan(int T, int B, int H, int n_cu, hipStream_t st, LstmSeqPlan* out) {
+  uint32_t words[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+  int bits = 0;
+  if (st && hipExtStreamGetCUMask(st, 8, words) == hipSuccess)
+    for (uint32_t w : words) bits += __builtin_popcount(w);
+  else if (st)
+    (void)hipGetLastError();
+  // (a launch planned for other CUs than the stream's: as for consecutive slots)
+  return lstm_seq_plan(T, B, H, n_cu, bits == n_cu ? words : static_cast<const uint32_t*>(nullptr), out);
 }
 
 size_t lstm_seq_exchange_bytes(int B, int H, const LstmSeqPlan& p) {
