@@ -655,10 +655,11 @@ dstack_status dstack_serve(const dstack_model* models, int n_models, const void*
  *   exchange h through the workspace; else one launch per step, its shape
  *   (hidden units per workgroup) chosen for those CUs.  The result is the same
  *   up to fp32 summation order.
- * lstm_layer_wait: lstm_layer with the time (us; 5000 there) that a workgroup
- *   of the one launch waits for the others' h.  Past it (other work holds the
- *   CUs so that not all of them run) one workgroup computes the sequence
- *   alone, tens of times slower; a negative value takes that path at once. */
+ * lstm_layer_wait: lstm_layer with the time (us; there 100 and 4 a step) that
+ *   a workgroup of the one launch waits for the others' h.  Past it (other
+ *   work holds the CUs so that not all of them run) the workgroups that run
+ *   compute the sequence from its start without the others; a negative value
+ *   takes that path at once. */
 dstack_status dstack_op_conv2d(const void* x, int N, int H, int W, int C, const void* w, int K, int R, int S,
                                int stride, int pad, const float* scale, const float* shift, const void* res, int act,
                                void* y, int out_fp32, void* stream);

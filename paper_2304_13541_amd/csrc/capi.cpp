@@ -1007,8 +1007,9 @@ dstack_status dstack_op_avgpool(const void* x, int N, int H, int W, int C, void*
 }
 
 // gx [T][B][4H] fp32 | c [B][H] fp32 | W_hh in fragment order [4H][H] bf16, or
-// the blocks' exchange of h (at most 4 (B + 1) H bytes) | h(t-1), h(t) in
-// fragment order [2][B][H] bf16, or two control words; each part 256-byte aligned
+// the blocks' exchange of h (at most 4 (B + 1) H bytes) and, in the part's last
+// 2304 bytes, their control words (8 H^2 - 2304 >= 132 H for H >= 32) | h(t-1),
+// h(t) in fragment order [2][B][H] bf16; each part 256-byte aligned
 static size_t align256z(size_t n) { return (n + 255) / 256 * 256; }
 size_t dstack_lstm_workspace_bytes(int T, int B, int H) {
   if (T <= 0 || B <= 0 || H <= 0) return 0;
@@ -1045,10 +1046,11 @@ dstack_status dstack_op_lstm_layer_wait(const void* x, int T, int B, int I, int 
     p += align256z((size_t)B * H * 4);
     bf16* wp = reinterpret_cast<bf16*>(p);
     p += align256z((size_t)4 * H * H * 2);
+    unsigned* ctl = reinterpret_cast<unsigned*>(p - LSTM_SEQ_CTL_BYTES);
     bf16* hp = reinterpret_cast<bf16*>(p);
     return lstm_layer_run(static_cast<const bf16*>(x), T, B, I, H, static_cast<const bf16*>(w_ih),
                           static_cast<const bf16*>(w_hh), nullptr, bias, static_cast<bf16*>(h_bf16), h_f32, gx, c,
-                          wp, hp, wp, reinterpret_cast<unsigned*>(hp), wait_us * 100L,
+                          wp, hp, wp, ctl, wait_us * 100L,
                           stream_cu_count((hipStream_t)stream), (hipStream_t)stream, nullptr);
   });
 }
@@ -1056,7 +1058,7 @@ dstack_status dstack_op_lstm_layer_wait(const void* x, int T, int B, int I, int 
 dstack_status dstack_op_lstm_layer(const void* x, int T, int B, int I, int H, const void* w_ih, const void* w_hh,
                                    const float* bias, void* h_bf16, float* h_f32, void* workspace, void* stream) {
   return dstack_op_lstm_layer_wait(x, T, B, I, H, w_ih, w_hh, bias, h_bf16, h_f32, workspace,
-                                   (int)(LSTM_SEQ_LIMIT / 100), stream);
+                                   (int)(lstm_seq_limit(T) / 100), stream);
 }
 
 dstack_status dstack_op_embed_ln(const int32_t* ids, int rows, int T, int vocab, const void* we, const void* pe,

@@ -200,11 +200,15 @@ struct LstmSeqPlan {
 bool lstm_seq_plan(int T, int B, int H, int n_cu, const uint32_t* mask, LstmSeqPlan* out);
 bool lstm_seq_plan(int T, int B, int H, int n_cu, hipStream_t st, LstmSeqPlan* out);
 size_t lstm_seq_exchange_bytes(int B, int H, const LstmSeqPlan& p);  // <= 4 (B + 1) H
-// whh row-major; c: [B][H] scratch; ctl: two words; limit: how long a block
-// waits for the others' h, in ticks of 10 ns (negative: gives up at once).
-constexpr long LSTM_SEQ_LIMIT = 500000;
+// whh row-major; c: [B][H], exchange and hp: [2][B][H] scratch; ctl:
+// LSTM_SEQ_CTL_BYTES of control words; limit: how long a block waits for the
+// others' h, in ticks of 10 ns (negative: gives up at once).
+constexpr size_t LSTM_SEQ_CTL_BYTES = 2304;
+// The wait of a layer that names none: 100 us and 4 us a step, long enough for
+// another such sequence to leave the CUs that both use.
+constexpr long lstm_seq_limit(int T) { return 10000L + 400L * T; }
 dstack_status launch_lstm_seq(const float* gx, const bf16* whh, bf16* h, float* hf, float* c, void* exchange,
-                              unsigned* ctl, int T, int B, int H, const LstmSeqPlan& p, long limit, hipStream_t st);
+                              bf16* hp, unsigned* ctl, int T, int B, int H, const LstmSeqPlan& p, long limit, hipStream_t st);
 dstack_status launch_probe(uint32_t* d_out, int n_blocks, hipStream_t st);
 
 }  // namespace dstack

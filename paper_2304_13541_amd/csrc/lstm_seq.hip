@@ -24,14 +24,18 @@
 //
 // Waiting.  The blocks of a group must run at the same time, so the plan asks
 // for no more blocks than the dispatcher places at once (lstm_seq_blocks).
-// If others hold the CUs all the same (two such kernels started on
-// overlapping partitions, each resident in part), every wait is bounded: it
-// gives up after `limit` or when another wave did, all blocks leave, and the
-// last to leave runs the sequence alone (lstm_serial: slow, but it waits for
-// nobody).
+// If others hold the CUs all the same (recurrences released together on
+// CUs that they share, each resident in part), every wait is bounded: it gives
+// up after `limit` or when another wave did, and the blocks that run compute
+// the sequence from its start as shared work, without the others (lstm_shared).
+// Measured with 50 steps, B = 32, H = 1024: two layers released together on 16
+// slots each, 8 of them shared, 0.39 ms (0.46 by one launch per step), four on
+// the same 16 slots, of which three give up, 2.1 ms (0.86); shared work alone
+// takes 0.55 ms, 11 us a step.
 #include <algorithm>
 
 #include "common.hpp"
+#include "conv_common.hpp"
 
 namespace dstack {
 
@@ -39,78 +43,156 @@ namespace {
 
 constexpr int LS_WAVES = 8;
 constexpr int LS_THREADS = 64 * LS_WAVES;
-constexpr int LS_SC1 = 16;  // buffer cache policy: device scope (past the per-XCD L2)
+constexpr int LS_TS = 1024 + 128;  // LDS bytes of one 16 x 16 partial tile (padded: adjacent tiles, other banks)
+
+// control words: [1] a wait gave up; from these on, steps done and taken of each block's rows and items
+constexpr int LS_DONE = 64, LS_TAKEN = LS_DONE + 256;
 
 struct LstmSeqArgs {
   const float* gx;   // [T][B][4H]
   const bf16* whh;   // [4H][H]
   bf16* h;           // [T][B][H]
   float* hf;         // [T][B][H] or null
-  float* c;          // [B][H]: cell state of the serial path only
+  float* c;          // [B][H]: cell state (shared work only)
   unsigned* xch;     // exchanged h, two slots of groups * H * bg bf16
-  unsigned* ctl;     // [0] blocks done, [1] a wait gave up
+  unsigned short* hp;  // h of shared work, two slots of [H/32][B][32] bf16
+  unsigned* ctl;     // control words
   int T, B, H, groups, bg, blocks;
   long limit;        // ticks (10 ns) a wait may last
 };
 
 __device__ __forceinline__ unsigned bf16_bits(bf16 v) { return (unsigned)__builtin_bit_cast(unsigned short, v); }
 
-// The whole recurrence by one block, without waiting for any other (a wave
-// takes row tiles wave, wave + 8, ...; loads of 8 depth steps in flight).
-__device__ void lstm_serial(const LstmSeqArgs& a) {
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int H = a.H, B = a.B, quad = lane >> 4, col = lane & 15, nks = H >> 5, tiles = H >> 2;
-  for (int t = 0; t < a.T; ++t) {
-    for (int bt = 0; bt < B; bt += 16)
-      for (int rt = wave; rt < tiles; rt += LS_WAVES) {
-        f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-        const int b = min(bt + col, B - 1);
-        const bf16* wr = a.whh + (long)((col >> 2) * H + 4 * rt + (col & 3)) * H + quad * 8;
-        const bf16* hr = a.h + ((long)(t - 1) * B + b) * H + quad * 8;
-        if (t > 0)
-          for (int s0 = 0; s0 < nks; s0 += 8) {
-            bf16x8 wv[8], hv[8];
+// The recurrence as shared work, when a wait gave up.  A unit is one step of
+// one block's rows and items; two words of each block's unit count the steps
+// taken and done.  The current step is the least that is done of any unit; a
+// block takes its own unit of it (whose weights its XCD's L2 holds), else one
+// that nobody took: that of a block which does not run.  Every wait ends,
+// however few of the launch's blocks run: a taken unit belongs to a block that
+// runs, and a running block takes what is left of the current step before it
+// waits.  Blocks that start later join.  h goes through hp and c through memory
+// (device scope, complete before the unit counts as done); what blocks that
+// have not yet noticed write to h and hf meanwhile are the same values up to
+// summation order.
+template <int RT, int KSW>
+__device__ void lstm_shared(const LstmSeqArgs& a, unsigned char* red, int* pick) {
+  constexpr int CELLS = RT * 4 * 16;
+  const int tid = threadIdx.x, lane = tid & 63, quad = lane >> 4, col = lane & 15;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // scalar: products past the depth are branched around
+  const int H = a.H, B = a.B, nks = H >> 5, k0 = wave * KSW, own = blockIdx.x;
+  const int slot_elems = B * H;
+  const __amdgpu_buffer_rsrc_t hr = __builtin_amdgcn_make_buffer_rsrc(a.hp, (short)0, slot_elems * 4, 0x00020000);
+  unsigned* const done = a.ctl + LS_DONE;
+  unsigned* const taken = a.ctl + LS_TAKEN;
+  const int cb = (tid >> 3) & 15, cu = (tid >> 7) * 8 + (tid & 7);  // the thread's cell, as in the kernel
+  auto wave_min = [](int v) __attribute__((always_inline)) {
 #pragma unroll
-            for (int s = 0; s < 8; ++s) {
-              const bool in = s0 + s < nks;
-              wv[s] = in ? *reinterpret_cast<const bf16x8*>(wr + (s0 + s) * 32) : bf16x8{};
-              hv[s] = in ? *reinterpret_cast<const bf16x8*>(hr + (s0 + s) * 32) : bf16x8{};
-            }
+    for (int o = 32; o >= 1; o >>= 1) v = min(v, __shfl_xor(v, o, 64));
+    return __builtin_amdgcn_readfirstlane(v);
+  };
+  // The loops' control is scalar and barriers enclose the divergent branches of
+  // this one: were one joined with another across the back edge, its lanes
+  // would circle alone, barriers included, and never end.
+  for (;;) {
+    __syncthreads();  // partial sums, flags and pick have been read
+    if (wave == 0) {
+      int t, unit = -1;
+      for (;;) {
+        int least = a.T, key = 0x7fffffff;
+        unsigned tk[4];
 #pragma unroll
-            for (int s = 0; s < 8; ++s) acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wv[s], hv[s], acc, 0, 0, 0);
-          }
-        // lane (quad g, column b) holds gate g of units 0..3; gather the four gates of unit `quad`
-        float g4[4];
-#pragma unroll
-        for (int g = 0; g < 4; ++g) {
-          float v = 0.f;
-#pragma unroll
-          for (int i = 0; i < 4; ++i) {
-            const float s = __shfl(acc[i], g * 16 + col, 64);
-            if (i == quad) v = s;
-          }
-          g4[g] = v;
+        for (int j = 0; j < 4; ++j) {
+          const int m = lane + 64 * j;
+          const bool in = m < a.blocks;
+          tk[j] = in ? __hip_atomic_load(taken + m, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : ~0u;
+          if (in) least = min(least, (int)__hip_atomic_load(done + m, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
         }
-        if (bt + col < B) {
-          const int j = 4 * rt + quad;
-          const long cell = (long)b * H + j;
+        t = wave_min(least);
+        if (t >= a.T) break;
+        // the own unit first, the others in an order that differs from block to block
 #pragma unroll
-          for (int g = 0; g < 4; ++g) g4[g] += a.gx[((long)t * B + b) * 4 * H + g * H + j];
-          float cv = t > 0 ? a.c[cell] : 0.f, hv;
-          lstm_cell(g4, cv, hv);
-          a.c[cell] = cv;
-          a.h[(long)t * B * H + cell] = (bf16)hv;
-          if (a.hf) a.hf[(long)t * B * H + cell] = hv;
+        for (int j = 0; j < 4; ++j) {
+          const int m = lane + 64 * j;
+          if (tk[j] == (unsigned)t) key = min(key, m == own ? m : ((m * 97 + own * 61 & 255) + 1) << 8 | m);
+        }
+        key = wave_min(key);
+        if (key == 0x7fffffff) continue;  // all taken: wait
+        unsigned was = (unsigned)t;
+        if (lane == 0)
+          __hip_atomic_compare_exchange_strong(taken + (key & 255), &was, (unsigned)t + 1, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                               __HIP_MEMORY_SCOPE_AGENT);
+        if (__builtin_amdgcn_readfirstlane((int)was) == t) {
+          unit = key & 255;
+          break;
         }
       }
-    __threadfence();
+      *(volatile int*)&pick[0] = t;
+      *(volatile int*)&pick[1] = unit;
+    }
     __syncthreads();
+    const int t = __builtin_amdgcn_readfirstlane(*(volatile int*)&pick[0]);
+    const int unit = __builtin_amdgcn_readfirstlane(*(volatile int*)&pick[1]);
+    if (unit < 0) return;
+    const int grp = unit % a.groups, rt0 = unit / a.groups * RT;
+    const int b0 = grp * a.bg, nb = min(a.bg, B - b0);
+    const int cj = 4 * rt0 + cu, item = b0 + cb;
+    const bool mine = tid < CELLS && cb < nb;
+    const long cell = (long)item * H + cj;
+    float g4[4], cst = 0.f;
+#pragma unroll
+    for (int g = 0; g < 4; ++g) g4[g] = mine ? a.gx[((long)t * B + item) * 4 * H + g * H + cj] : 0.f;
+    if (t > 0) {
+      const int slot = ((t - 1) & 1) * slot_elems * 2, b = b0 + min(col, nb - 1);
+      if (mine) cst = __hip_atomic_load(a.c + cell, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      bf16x8 x[KSW];
+#pragma unroll
+      for (int s = 0; s < KSW; ++s)
+        if (k0 + s < nks)
+          x[s] = __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(
+                                                hr, (((k0 + s) * B + b) * 32 + quad * 8) * 2, slot, CPOL_SC1));
+#pragma unroll
+      for (int i = 0; i < RT; ++i) {
+        const bf16* wr = a.whh + (long)((col >> 2) * H + 4 * (rt0 + i) + (col & 3)) * H + k0 * 32 + quad * 8;
+        f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int s = 0; s < KSW; ++s)
+          if (k0 + s < nks)
+            acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(*reinterpret_cast<const bf16x8*>(wr + s * 32), x[s], acc, 0, 0, 0);
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+          *reinterpret_cast<float*>(red + (wave * RT + i) * LS_TS + (u * 16 + col) * 16 + quad * 4) = acc[u];
+      }
+    }
+    __syncthreads();
+    if (mine) {
+      if (t > 0) {
+        f32x4 v[LS_WAVES];
+#pragma unroll
+        for (int q = 0; q < LS_WAVES; ++q)
+          v[q] = *reinterpret_cast<const f32x4*>(red + (q * RT + (cu >> 2)) * LS_TS + ((cu & 3) * 16 + cb) * 16);
+        const f32x4 sum = ((v[0] + v[1]) + (v[2] + v[3])) + ((v[4] + v[5]) + (v[6] + v[7]));
+#pragma unroll
+        for (int g = 0; g < 4; ++g) g4[g] += sum[g];
+      }
+      float hn;
+      lstm_cell(g4, cst, hn);
+      const bf16 hb = (bf16)hn;
+      __hip_atomic_store(a.hp + (t & 1) * slot_elems + ((cj >> 5) * B + item) * 32 + (cj & 31),
+                         __builtin_bit_cast(unsigned short, hb), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      __hip_atomic_store(a.c + cell, cst, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      const long o = (long)t * B * H + cell;
+      a.h[o] = hb;
+      if (a.hf) a.hf[o] = hn;
+    }
+    wait_vmcnt<0>();  // the wave's stores have reached device scope
+    __syncthreads();
+    if (wave == 0) __hip_atomic_store(done + unit, (unsigned)(t + 1), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
 }
 
 template <int RT, int KSW>
 __global__ __launch_bounds__(LS_THREADS, RT <= 4 && RT * KSW <= 8 ? 4 : 2) void lstm_seq_kernel(LstmSeqArgs a) {
-  constexpr int TS = 1024 + 128;            // LDS bytes of one 16 x 16 partial tile (padded: adjacent tiles, other banks)
+  constexpr int TS = LS_TS;
   constexpr int BUF = LS_WAVES * RT * TS;   // partial sums of one step
   constexpr int CELLS = RT * 4 * 16;
   static_assert(CELLS <= LS_THREADS, "one thread per cell");
@@ -118,7 +200,8 @@ __global__ __launch_bounds__(LS_THREADS, RT <= 4 && RT * KSW <= 8 ? 4 : 2) void 
   // by step modulo 3: items whose h(t-1) holds a NaN (bits 0..15), and
   // whether a wave gave up waiting (bit 16)
   __shared__ int flags[3];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, quad = lane >> 4, col = lane & 15;
+  const int tid = threadIdx.x, lane = tid & 63, quad = lane >> 4, col = lane & 15;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // scalar: products past the depth are branched around
   const int H = a.H, nks = H >> 5, tiles = H >> 2;
   const int grp = blockIdx.x % a.groups, rank = blockIdx.x / a.groups;
   const int b0 = grp * a.bg, nb = min(a.bg, a.B - b0);  // the group's batch items
@@ -155,7 +238,7 @@ __global__ __launch_bounds__(LS_THREADS, RT <= 4 && RT * KSW <= 8 ? 4 : 2) void 
   const int woff = (int)((unsigned)(grp * H * a.bg + ((cj >> 3) * a.bg + cb) * 8 + (cj & 7)) * 2u);
 
   __syncthreads();
-  bool dead = false;
+  bool dead = false, gave_up = false;
   for (int t = 0, t3 = 0; t < a.T; ++t, t3 = t3 == 2 ? 0 : t3 + 1) {
     unsigned char* rb = red + (t & 1) * BUF;
     if (t > 0) {
@@ -167,7 +250,7 @@ __global__ __launch_bounds__(LS_THREADS, RT <= 4 && RT * KSW <= 8 ? 4 : 2) void 
 #pragma unroll
         for (int s = 0; s < KSW; ++s)
           if (k0 + s < nks) {
-            const uint4 v = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(xr, xoff + s * kstep_bytes, slot, LS_SC1));
+            const uint4 v = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(xr, xoff + s * kstep_bytes, slot, CPOL_SC1));
             d[s][0] = v.x; d[s][1] = v.y; d[s][2] = v.z; d[s][3] = v.w;
           }
       };
@@ -184,9 +267,9 @@ __global__ __launch_bounds__(LS_THREADS, RT <= 4 && RT * KSW <= 8 ? 4 : 2) void 
       for (int spin = 0;; ++spin) {
         load(x);
         if (ready(x)) break;
-        if ((spin & 63) == 0) {  // bounded: give up after `limit`, or when another wave did
+        if ((spin & 15) == 15 || a.limit < 0) {  // bounded: give up after `limit`, or when another wave did
           const long now = (long)__builtin_amdgcn_s_memrealtime();
-          if (spin == 0) t0 = now;
+          if (spin <= 15) t0 = now;
           if (now - t0 > a.limit || __hip_atomic_load(a.ctl + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) {
             dead = true;
             break;
@@ -228,7 +311,7 @@ __global__ __launch_bounds__(LS_THREADS, RT <= 4 && RT * KSW <= 8 ? 4 : 2) void 
           *reinterpret_cast<float*>(rb + (wave * RT + i) * TS + (u * 16 + col) * 16 + quad * 4) = acc[i][u];
     }
     __syncthreads();
-    const int flag = *(volatile int*)&flags[t3];
+    const int flag = __builtin_amdgcn_readfirstlane(*(volatile int*)&flags[t3]);
     float g4[4] = {gxv[0], gxv[1], gxv[2], gxv[3]};
     if (t > 0 && wave * 64 < CELLS) {
       f32x4 v[LS_WAVES];
@@ -238,7 +321,10 @@ __global__ __launch_bounds__(LS_THREADS, RT <= 4 && RT * KSW <= 8 ? 4 : 2) void 
 #pragma unroll
       for (int g = 0; g < 4; ++g) g4[g] += sum[g];
     }
-    if (flag >> 16) break;  // block-uniform: written before the barrier
+    if (flag >> 16) {  // the same in all waves: written before the barrier
+      gave_up = true;
+      break;
+    }
     // read by all before this step's barrier, set again after the next one's
     if (tid == 0) *(volatile int*)&flags[t3 == 0 ? 2 : t3 - 1] = 0;
     if (wave * 64 >= CELLS) continue;  // wave-uniform: no cells
@@ -257,7 +343,7 @@ __global__ __launch_bounds__(LS_THREADS, RT <= 4 && RT * KSW <= 8 ? 4 : 2) void 
       const unsigned r1 = __builtin_amdgcn_mov_dpp(q1, 0x141, 0xf, 0xf, true);
       typedef __attribute__((__vector_size__(4 * sizeof(unsigned)))) unsigned u32x4;
       if (mine && (lane & 7) == 0)
-        __builtin_amdgcn_raw_buffer_store_b128((u32x4{q0, q1, r0, r1}), xr, woff, (int)((t & 1) * slot_elems * 2u), LS_SC1);
+        __builtin_amdgcn_raw_buffer_store_b128((u32x4{q0, q1, r0, r1}), xr, woff, (int)((t & 1) * slot_elems * 2u), CPOL_SC1);
     }
     if (mine) {
       if (t + 1 < a.T) {
@@ -270,22 +356,15 @@ __global__ __launch_bounds__(LS_THREADS, RT <= 4 && RT * KSW <= 8 ? 4 : 2) void 
       if (a.hf) a.hf[o] = hn;
     }
   }
-  // the last block to finish redoes the sequence alone if any wait gave up
-  __syncthreads();
-  if (tid == 0) {
-    __threadfence();
-    flags[0] = (int)__hip_atomic_fetch_add(a.ctl, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) == a.blocks - 1 &&
-           __hip_atomic_load(a.ctl + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  }
-  __syncthreads();
-  if (flags[0]) lstm_serial(a);
+  if (gave_up) lstm_shared<RT, KSW>(a, red, flags);
 }
 
-// marks both slots as not yet written (bit 14 set: the parity of t / 2 = 1), clears the two control words
+// marks both slots as not yet written (bit 14 set: the parity of t / 2 = 1), clears the control words
+static_assert(LSTM_SEQ_CTL_BYTES == (LS_TAKEN + 256) * 4, "a plan has at most 256 blocks");
 __global__ __launch_bounds__(256) void lstm_seq_clear_kernel(unsigned* xch, int n, unsigned* ctl) {
   const int i = blockIdx.x * 256 + threadIdx.x;
   if (i < n) xch[i] = 0x40004000u;
-  if (i < 2) ctl[i] = 0u;
+  if (i < LSTM_SEQ_CTL_BYTES / 4) ctl[i] = 0u;
 }
 
 }  // namespace
@@ -365,12 +444,14 @@ size_t lstm_seq_exchange_bytes(int B, int H, const LstmSeqPlan& p) {
 }
 
 dstack_status launch_lstm_seq(const float* gx, const bf16* whh, bf16* h, float* hf, float* c, void* exchange,
-                              unsigned* ctl, int T, int B, int H, const LstmSeqPlan& p, long limit, hipStream_t st) {
+                              bf16* hp, unsigned* ctl, int T, int B, int H, const LstmSeqPlan& p, long limit, hipStream_t st) {
   DS_CHECK(B >= 1 && B <= 32 && H % 32 == 0 && H >= 32 && H <= 2048, DSTACK_E_UNSUPPORTED, "lstm: bad shape");
-  LstmSeqArgs a{gx, whh, h, hf, c, static_cast<unsigned*>(exchange), ctl, T, B, H, p.groups,
+  LstmSeqArgs a{gx, whh, h, hf, c, static_cast<unsigned*>(exchange), reinterpret_cast<unsigned short*>(hp), ctl,
+                T, B, H, p.groups,
                 (B + p.groups - 1) / p.groups, p.blocks, limit};
   const int words = (int)(lstm_seq_exchange_bytes(B, H, p) / 4);
-  launch(lstm_seq_clear_kernel, dim3((words + 255) / 256), dim3(256), 0, st, a.xch, words, ctl);
+  launch(lstm_seq_clear_kernel, dim3((std::max(words, (int)LSTM_SEQ_CTL_BYTES / 4) + 255) / 256), dim3(256), 0, st, a.xch,
+         words, ctl);
   DS_HIP(hipGetLastError());
   const int ksw = (H / 32 + LS_WAVES - 1) / LS_WAVES;
   if (ksw <= 1)

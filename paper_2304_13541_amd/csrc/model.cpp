@@ -680,7 +680,7 @@ dstack_status get_workspace(Model& m, int pid, int n_cu, hipStream_t st, Workspa
   total += align256(sk);
   const size_t cnt_off = total;
   if (sk) total += align256(SPLITK_TILE_COUNTERS * sizeof(unsigned));
-  size_t gx_off = 0, c_off = 0, h0_off = 0, h1_off = 0, hp_off = 0, ctl_off = 0;
+  size_t gx_off = 0, c_off = 0, h0_off = 0, h1_off = 0, hp_off = 0, xch_off = 0, ctl_off = 0;
   if (m.is_lstm) {
     gx_off = total;
     total += align256((size_t)m.lstm_T * m.max_batch * 4 * m.lstm_H * 4);
@@ -692,8 +692,10 @@ dstack_status get_workspace(Model& m, int pid, int n_cu, hipStream_t st, Workspa
     total += align256((size_t)m.lstm_T * m.max_batch * m.lstm_H * 2);
     hp_off = total;
     total += align256((size_t)2 * m.max_batch * m.lstm_H * 2);
+    xch_off = total;
+    total += align256((size_t)4 * (m.max_batch + 1) * m.lstm_H);
     ctl_off = total;
-    total += 256;
+    total += LSTM_SEQ_CTL_BYTES;
   }
   DS_HIP(hipMalloc(&w->base, total));
   w->bytes = total;
@@ -719,6 +721,7 @@ dstack_status get_workspace(Model& m, int pid, int n_cu, hipStream_t st, Workspa
     w->lstm_h[0] = (bf16*)(base + h0_off);
     w->lstm_h[1] = (bf16*)(base + h1_off);
     w->lstm_hp = (bf16*)(base + hp_off);
+    w->lstm_xch = base + xch_off;
     w->lstm_ctl = (unsigned*)(base + ctl_off);
   }
   *out = w.get();
@@ -812,7 +815,7 @@ dstack_status lstm_layer_run(const bf16* x, int T, int B, int I, int H, const bf
   LstmSeqPlan seq;
   if (lstm_seq_plan(T, B, H, n_cu, st, &seq)) {
     if (timer) timer->before();
-    s = launch_lstm_seq(gx, w_hh, h_bf16, h_f32, c, exchange, ctl, T, B, H, seq, wait_limit, st);
+    s = launch_lstm_seq(gx, w_hh, h_bf16, h_f32, c, exchange, hp, ctl, T, B, H, seq, wait_limit, st);
     if (s != DSTACK_OK) return s;
     if (timer)
       timer->after(KC_LSTM, 2.0 * T * B * H * 4.0 * H,
@@ -866,8 +869,8 @@ dstack_status forward(Model& m, int batch, const void* d_in, void* d_out, Worksp
       bf16* hb = op.in == BUF_IN ? ws.lstm_h[0] : ws.lstm_h[1];
       float* hf = op.out == BUF_OUT ? (float*)d_out : nullptr;
       s = lstm_layer_run(x, op.T, batch, op.I, op.Hd, m.d_w + op.wih_off, m.d_w + op.whh_off, m.d_wp + op.wp_off,
-                         f32 + op.bias_off, hb, hf, ws.lstm_gx, ws.lstm_c, nullptr, ws.lstm_hp, ws.lstm_hp, ws.lstm_ctl,
-                         LSTM_SEQ_LIMIT, n_cu, st, timer);
+                         f32 + op.bias_off, hb, hf, ws.lstm_gx, ws.lstm_c, nullptr, ws.lstm_hp, ws.lstm_xch, ws.lstm_ctl,
+                         lstm_seq_limit(op.T), n_cu, st, timer);
       if (s != DSTACK_OK) return s;
       continue;
     }

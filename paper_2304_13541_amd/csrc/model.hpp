@@ -80,8 +80,9 @@ struct Workspace {
   float* lstm_gx = nullptr;
   float* lstm_c = nullptr;
   bf16* lstm_h[2] = {nullptr, nullptr};
-  bf16* lstm_hp = nullptr;  // h(t-1), h(t) in fragment order (2 x max batch x H), or exchanged between blocks
-  unsigned* lstm_ctl = nullptr;  // control words of the one-launch recurrence
+  bf16* lstm_hp = nullptr;       // h(t-1), h(t) in fragment order (2 x max batch x H)
+  void* lstm_xch = nullptr;      // h exchanged between the blocks of the one-launch recurrence
+  unsigned* lstm_ctl = nullptr;  // its control words
   std::atomic<bool> busy{false};
   // captured forward passes, keyed by (batch, input, output, CUs of the
   // partition); replayed with one hipGraphLaunch
@@ -182,10 +183,10 @@ dstack_status launch_conv2d_ws(const bf16* x, int N, int H, int W, int C, const 
                                int act, void* y, bool out_fp32, int n_cu, float* splitk_ws, size_t splitk_bytes,
                                unsigned* tile_counters, hipStream_t st);
 // One LSTM layer.  The recurrence runs in one launch where lstm_seq_plan
-// allows it (w_hh row-major; exchange of lstm_seq_exchange_bytes and two
-// control words at ctl), else step by step: whh_packed is W_hh already in
+// allows it (w_hh row-major; exchange of lstm_seq_exchange_bytes,
+// LSTM_SEQ_CTL_BYTES at ctl), else step by step: whh_packed is W_hh already in
 // fragment order (a model's, packed at load), or NULL: w_hh is packed into
-// wp_scratch (4H x H) first.  hp may be the exchange, wp_scratch too.
+// wp_scratch (4H x H) first.  wp_scratch may hold the exchange and ctl.
 dstack_status lstm_layer_run(const bf16* x, int T, int B, int I, int H, const bf16* w_ih, const bf16* w_hh,
                              const bf16* whh_packed, const float* bias, bf16* h_bf16, float* h_f32, float* gx,
                              float* c, bf16* wp_scratch, bf16* hp, void* exchange, unsigned* ctl, long wait_limit,

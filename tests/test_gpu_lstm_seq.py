@@ -6,8 +6,8 @@ The cases sit at the edges of its plan: one item, a full and a just
 overfull batch slice (16 / 17), ragged slices, one depth step (H = 32), idle
 waves (H = 96), the widest rows (H = 2048), partitions that hold the rows in
 8, 4 and 2 tiles per workgroup, and engines of unequal size (5 and 10 slots).
-Also: NaN inputs stay in their item, a wait that gives up at once, replays of
-a captured launch.
+Also: NaN inputs stay in their item, a wait that gives up at once, layers that
+share CUs, replays of a captured launch.
 
 Bar: h is a bf16 rounding apart from the oracle's at each step (2^-9), fed
 back through gates of slope <= 1: infinity-norm relative error <= 2^-7."""
@@ -61,6 +61,14 @@ class Layer:
 
     def run(self, stream=None, **kw):
         self.env[0].lstm_layer(*self.dev, self.hb, self.hf, self.ws, stream=stream, **kw)
+
+    def control(self):
+        """(a wait gave up, steps done of each workgroup's rows) from the workspace's control words: the last 2304
+        bytes of the part that holds the exchange; (0, zeros) where the one launch went through by itself."""
+        T, B, _, H = self.shape
+        end = sum((n + 255) // 256 * 256 for n in (T * B * 16 * H, B * H * 4, 8 * H * H))
+        w = self.ws[end - 2304:end].cpu().numpy().view(np.int32)
+        return int(w[1]), w[64:320]
 
     def result(self):
         self.env[4].cuda.synchronize()
@@ -117,15 +125,67 @@ def test_nan_stays_in_its_item(env):
         assert env[3].rel_err(v[~want], ref[~want]) <= TOL
 
 
-def test_wait_that_gives_up(env):
-    """With no time to wait, one workgroup computes the sequence alone; the workspace then serves the normal path."""
-    layer = Layer(env, 6, 18, 32, 128)
+@pytest.mark.parametrize("B,H,slots", [(18, 128, None), (32, 1024, 16), (5, 256, 2), (17, 96, 1), (9, 1056, None)])
+def test_wait_that_gives_up(env, B, H, slots):
+    """With no time to wait, the workgroups that run compute the sequence as shared work; the workspace then serves
+    the normal path."""
+    T = 6
+    layer = Layer(env, T, B, 32, H)
     ref = layer.ref()
-    for wait in (-1, None, -1, 5000):
-        layer.hf.fill_(7.0)
-        layer.run(wait_us=wait)
-        hb, hf = layer.result()
-        assert env[3].rel_err(hf, ref) <= TOL and env[3].rel_err(hb, ref) <= TOL
+    blocks = env[0].lstm_plan(T, B, H, 8 * slots if slots else 256)[1]
+    part = env[0].Partition(slot_offset=0, n_slots=slots) if slots else None
+    try:
+        for wait in (-1, None, -1, 5000):
+            layer.hf.fill_(7.0)
+            layer.run(part.stream_ptr if part else None, wait_us=wait)
+            hb, hf = layer.result()
+            assert env[3].rel_err(hf, ref) <= TOL and env[3].rel_err(hb, ref) <= TOL
+            gave_up, done = layer.control()
+            assert gave_up == (wait == -1) and np.all(done[blocks:] == 0)
+            assert np.all(done[:blocks] == (T if wait == -1 else 0))
+    finally:
+        if part:
+            part.destroy()
+
+
+@pytest.mark.parametrize("offsets,wait", [((0, 8, 4, 12), None), ((0, 0, 0, 0), None), ((0, 8, 4, 12), 50)])
+def test_layers_that_share_cus(env, offsets, wait):
+    """Four recurrences released at once on CUs that they share, so that each may hold a part of them: whichever wait
+    gives up, the results hold, and the wait and the shared work take a few milliseconds (bar: 20; all the work on one
+    CU takes over 50)."""
+    torch, ds = env[4], env[0]
+    layers = [Layer(env, 50, 32, 32, 1024) for _ in offsets]
+    ref = layers[0].ref()
+    parts = [ds.Partition(slot_offset=o, n_slots=16) for o in offsets]
+    try:
+        streams = [torch.cuda.ExternalStream(p.stream_ptr) for p in parts]
+        gate, big = torch.cuda.Stream(), torch.zeros(1 << 28, device="cuda:0")
+        for rep in range(4):
+            for layer in layers:
+                layer.hf.fill_(7.0)
+            torch.cuda.synchronize()
+            start = torch.cuda.Event(enable_timing=True)
+            ends = [torch.cuda.Event(enable_timing=True) for _ in parts]
+            with torch.cuda.stream(gate):
+                for _ in range(3):
+                    big.add_(1.0)
+                start.record()
+            for s in streams:
+                s.wait_event(start)
+            for layer, p, s, e in zip(layers, parts, streams, ends):
+                layer.run(p.stream_ptr, wait_us=wait)
+                e.record(s)
+            results = [layer.result() for layer in layers]
+            ms = max(start.elapsed_time(e) for e in ends)
+            state = [layer.control() for layer in layers]
+            print("  released together:", offsets, wait, "%.2f ms," % ms, "gave up", [s[0] for s in state], flush=True)
+            for (hb, hf), (gave_up, done) in zip(results, state):
+                assert env[3].rel_err(hf, ref) <= TOL and env[3].rel_err(hb, ref) <= TOL
+                assert np.all(done[:128] == (50 if gave_up else 0))
+            assert rep == 0 or ms < 20.0
+    finally:
+        for p in parts:
+            p.destroy()
 
 
 def test_replays_equal_eager(env):
