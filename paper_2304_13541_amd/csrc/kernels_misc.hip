@@ -189,7 +189,7 @@ __global__ __launch_bounds__(256) void maxpool_window_kernel(const bf16* __restr
 dstack_status launch_maxpool(const bf16* x, int N, int H, int W, int C, int k, int stride, int pad, bf16* y,
                              hipStream_t st) {
   DS_CHECK(C % 8 == 0, DSTACK_E_UNSUPPORTED, "maxpool: C must be a multiple of 8");
-  DS_CHECK(k > 0 && stride > 0 && pad >= 0 && pad < k && N > 0 && H > 0 && W > 0, DSTACK_E_INVALID,
+  DS_CHECK(k > 0 && stride > 0 && pad >= 0 && pad < k && N > 0 && H > 0 && W > 0 && C > 0, DSTACK_E_INVALID,
            "maxpool: bad shape");
   int Ho = out_dim(H, k, stride, pad), Wo = out_dim(W, k, stride, pad);
   DS_CHECK(Ho > 0 && Wo > 0, DSTACK_E_INVALID, "maxpool: empty output");

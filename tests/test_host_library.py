@@ -6,6 +6,8 @@ import math
 import os
 import random
 import re
+import subprocess
+import sys
 
 import numpy as np
 import pytest
@@ -244,3 +246,12 @@ def test_ideal_schedule_parity_random():
         ds.simulate_ideal([dict(slots=[40], dur=[5], batch=1, slo_us=10)], 100, 10)   # share above the total
     with pytest.raises(ds.DStackError):
         ds.simulate_ideal([dict(slots=[4], dur=[0], batch=1, slo_us=10)], 100, 10)    # zero duration
+
+
+def test_pool_of_no_channels_is_an_error():
+    """C = 0 (a multiple of 8) is refused like before the pools with 2x2 and 3x3 windows had their own kernel, in a
+    process of its own: a division by C / 8 on the host would end it."""
+    code = ("import ctypes, sys, paper_2304_13541_amd as ds; b = ctypes.create_string_buffer(64); "
+            "p = ctypes.cast(b, ctypes.c_void_p); "
+            "sys.exit(sum(ds.lib().dstack_op_maxpool(p, 1, 4, 4, 0, k, 2, 0, p, None) == ds.OK for k in (1, 2, 3)))")
+    assert subprocess.run([sys.executable, "-c", code], cwd=ROOT).returncode == 0
