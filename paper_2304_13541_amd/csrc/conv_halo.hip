@@ -18,7 +18,7 @@
 // one image (patch (th+2) x (tw+2), zeros around the image).  The 64 x 128
 // tile runs in blocks of 4 waves with 80 KB of LDS, two to a CU, so that one
 // block's start and epilogue (3-4 us of fixed latency) overlap the other's
-// products; the larger tiles run one block of 8 waves per CU; the 64 x 64
+// products; the 128 x 256 tile runs one block of 8 waves per CU; the 64 x 64
 // tile splits each 64-deep step between two groups of 4 waves (KG = 2), for
 // grids that leave CUs idle.
 //
@@ -457,21 +457,24 @@ __global__ __launch_bounds__(64 * WN * WM * KG) void conv_halo_kernel(HaloArgs a
 // ---- dispatch ----
 
 // Tile shapes: channels x pixels, ring stages, patch rows (less the zero row), blocks that
-// share a CU, whether a depth split is instantiated, and the estimate of a
-// block's time in us: fixed part and per 64-deep step, with one block on the
-// CU and with two (fit to MI355X timings of 9, 18, 36 and 72 steps).
+// share a CU, whether it has a depth split, and the estimate of a block's time
+// in us: fixed part and per 64-deep step, with one block on the CU and with two
+// (fit to MI355X timings of 9, 18, 36 and 72 steps).  Only the 64 x 64 tile
+// splits: the 64 x 128 tile's reduction needs 492 registers (one wave per SIMD
+// and a spill), so that its blocks did not share a CU (7 images of 50x50x768 ->
+// 176 on 240 CUs in two slices 106 us, unsplit in the general kernel 65; over
+// 60 shapes that took it the present choice takes 0.80 of its time).
 struct HaloTile {
   int bn, bm, stages, rows, per_cu;
   bool split;
   double fix1, step1, fix2, step2;
 };
 static constexpr HaloTile kHalo[] = {
-    {64, 128, 4, 191, 2, true, 3.25, 0.217, 4.15, 0.333},
+    {64, 128, 4, 191, 2, false, 3.25, 0.217, 4.15, 0.333},
     {64, 64, 6, 127, 2, true, 3.0, 0.152, 3.2, 0.232},
-    {128, 128, 4, 191, 1, false, 3.9, 0.342, 0, 0},
     {128, 256, 4, 383, 1, false, 6.9, 0.574, 0, 0},
 };
-constexpr int kHaloTiles = 4;
+constexpr int kHaloTiles = 3, kHaloLarge = 2, kHaloRest = 0;
 
 template <int BN, int BM, int WN, int WM, int KG, int STAGES, int NPG, bool CAN_SPLIT>
 static void halo_go(const HaloArgs& a, int splits, hipStream_t st, hipEvent_t e0, hipEvent_t e1) {
@@ -551,8 +554,8 @@ bool halo_plan(int N, int H, int W, int C, int K, int n_cu, bool can_split, size
   // that share all CUs, when the partly filled last round costs more than a
   // second launch (about 1.3 us).
   {
-    const HaloTile& t = kHalo[3];
-    const HaloTile& r = kHalo[0];
+    const HaloTile& t = kHalo[kHaloLarge];
+    const HaloTile& r = kHalo[kHaloRest];
     int th, tw, th2, tw2;
     long tm, tm2;
     if (K > 64 && N > 1 && halo_shape(t, N, H, W, &th, &tw, &tm)) {
@@ -564,7 +567,7 @@ bool halo_plan(int N, int H, int W, int C, int K, int n_cu, bool can_split, size
           halo_shape(r, N - n1, H, W, &th2, &tw2, &tm2)) {
         const int steps = chunks * HALO_TAPS;
         const double c = halo_cost(t, tm * tn, steps, n_cu) + 1.3 + halo_cost(r, tm2 * ceil_div(K, r.bn), steps, n_cu);
-        if (c < out->cost * 0.97) *out = HaloPlan{3, th, tw, 1, chunks, n1, 0, th2, tw2, c};
+        if (c < out->cost * 0.97) *out = HaloPlan{kHaloLarge, th, tw, 1, chunks, n1, kHaloRest, th2, tw2, c};
       }
     }
   }
@@ -606,9 +609,8 @@ void launch_halo(const bf16* x, int N, int H, int W, int C, const bf16* w, int K
     a.div_tiw = FastDiv::make(a.tiles_w);
     a.div_tih = FastDiv::make(a.tiles_h);
     switch (tile) {
-      case 0: halo_go<64, 128, 1, 4, 1, 4, 6, true>(a, p.splits, st, e0, e1); break;
+      case 0: halo_go<64, 128, 1, 4, 1, 4, 6, false>(a, p.splits, st, e0, e1); break;
       case 1: halo_go<64, 64, 1, 4, 2, 6, 2, true>(a, p.splits, st, e0, e1); break;
-      case 2: halo_go<128, 128, 2, 4, 1, 4, 3, false>(a, p.splits, st, e0, e1); break;
       default: halo_go<128, 256, 2, 4, 1, 4, 6, false>(a, p.splits, st, e0, e1); break;
     }
   };

@@ -60,6 +60,21 @@ def test_dispatch_rule():
         assert none["splits"] == 1 and none["workspace_bytes"] == 0
 
 
+def test_tiles_and_splits():
+    """The tiles that the kernel has, over the range of shapes; only 64 x 64 tiles split (a split 64 x 128 block needs
+    the registers of a whole CU, which the estimate of two blocks per CU does not count)."""
+    import paper_2304_13541_amd as ds
+    rng = np.random.default_rng(5)
+    seen = set()
+    for _ in range(4000):
+        N, H, W = (max(1, int(v)) for v in np.exp(rng.uniform(0, np.log([32, 112, 112]))))
+        C, K, n_cu = 64 * int(rng.integers(1, 13)), 8 * int(rng.integers(1, 97)), 8 * int(rng.integers(1, 33))
+        p = plan(ds, N, H, W, C, K, 1, n_cu)
+        if p["kernel"] == 2:
+            seen.add((p["tile_n"], p["tile_m"], p["splits"] > 1))
+    assert seen == {(64, 128, False), (64, 64, False), (64, 64, True), (128, 256, False)}
+
+
 @pytest.fixture(scope="module")
 def env(oracle_mod):
     import torch
