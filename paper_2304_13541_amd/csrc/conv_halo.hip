@@ -203,6 +203,36 @@ __global__ __launch_bounds__(64 * WN * WM * KG) void conv_halo_kernel(HaloArgs a
       pmask[j] = m < a.M ? (ho > 0 ? cols : 0u) | cols << 3 | (ho < a.H - 1 ? cols << 6 : 0u) : 0u;
     }
   }
+  // output pixel of local pixel pl (-1: none)
+  auto out_pixel = [&](int pl) __attribute__((always_inline)) {
+    if (a.tw > 0) {
+      const int ty = a.div_tw.div(pl), tx = pl - ty * a.tw;
+      const int h = h0 + ty, w = w0 + tx;
+      return ty < a.th && h < a.H && w < a.W ? (img * a.H + h) * a.W + w : -1;
+    }
+    return m0 + pl < a.M ? m0 + pl : -1;
+  };
+  // The lane's residual values.  A 64 x 128 tile loads them before its loop,
+  // where a round trip after it (0.8 us) is a tenth of a layer of one chunk: 91
+  // shapes with a residual take 0.957 of their time so, and from 1.26 to 1.07
+  // at most of the general kernel's.  The first steps' waits cover these loads,
+  // which are issued behind the first stages.  The large tile has no registers
+  // to spare for them and its 20 us of loop gain nothing (1.00, up to 1.05).
+  constexpr bool RES_EARLY = KG == 1 && !SPLIT && TM * TN <= 8;
+  bf16x4 resv[RES_EARLY ? TM : 1][TN] = {};
+  auto load_res = [&](int j, bf16x4 (&r)[TN]) __attribute__((always_inline)) {
+    const int px = max(out_pixel(wm * (BM / WM) + j * 16 + (lane & 15)), 0);
+#pragma unroll
+    for (int i = 0; i < TN; ++i) {
+      const int c = min(n0 + wn * (BN / WN) + i * 16 + (lane >> 4) * 4, a.K - 4);
+      r[i] = *reinterpret_cast<const bf16x4*>(a.res + ((long)px * a.K + c));
+    }
+  };
+  if constexpr (RES_EARLY)
+    if (a.res) {
+#pragma unroll
+      for (int j = 0; j < TM; ++j) load_res(j, resv[j]);
+    }
   const int arow = wn * (BN / WN) + (lane & 15);
   const int aaddr = arow * 128 + ((cq ^ ((arow >> 1) & 7)) << 4);
 
@@ -288,15 +318,6 @@ __global__ __launch_bounds__(64 * WN * WM * KG) void conv_halo_kernel(HaloArgs a
     par ^= 1;
   }
 
-  // output pixel of local pixel pl (-1: none)
-  auto out_pixel = [&](int pl) __attribute__((always_inline)) {
-    if (a.tw > 0) {
-      const int ty = a.div_tw.div(pl), tx = pl - ty * a.tw;
-      const int h = h0 + ty, w = w0 + tx;
-      return ty < a.th && h < a.H && w < a.W ? (img * a.H + h) * a.W + w : -1;
-    }
-    return m0 + pl < a.M ? m0 + pl : -1;
-  };
   const float hi = a.act == ACT_RELU6 ? 6.0f : INFINITY;
   // f(act) with the activation chosen once: none, a clamp to [0, hi] (ReLU:
   // hi = inf), GELU or tanh
@@ -316,11 +337,9 @@ __global__ __launch_bounds__(64 * WN * WM * KG) void conv_halo_kernel(HaloArgs a
     // tile then goes through LDS ([pixel][channel] rows of 16-byte units
     // swizzled by the pixel) to leave in 16-byte pieces of whole rows
     f32x4 sc[TN], sh[TN];
-    bool in[TN];
 #pragma unroll
     for (int i = 0; i < TN; ++i) {
-      const int c = n0 + wn * (BN / WN) + i * 16 + (lane >> 4) * 4, cc = min(c, a.K - 4);
-      in[i] = c < a.K;
+      const int cc = min(n0 + wn * (BN / WN) + i * 16 + (lane >> 4) * 4, a.K - 4);
       sc[i] = a.scale ? *reinterpret_cast<const f32x4*>(a.scale + cc) : f32x4{1.f, 1.f, 1.f, 1.f};
       sh[i] = a.shift ? *reinterpret_cast<const f32x4*>(a.shift + cc) : f32x4{0.f, 0.f, 0.f, 0.f};
     }
@@ -333,15 +352,15 @@ __global__ __launch_bounds__(64 * WN * WM * KG) void conv_halo_kernel(HaloArgs a
 #pragma unroll
       for (int j = 0; j < TM; ++j) {
         const int pl = wm * (BM / WM) + j * 16 + (lane & 15);
-        const int px = a.res ? max(out_pixel(pl), 0) : 0;
+        bf16x4 (&r4)[TN] = resv[RES_EARLY ? j : 0];
+        if constexpr (!RES_EARLY)
+          if (a.res) load_res(j, r4);
 #pragma unroll
         for (int i = 0; i < TN; ++i) {
           const int c = wn * (BN / WN) + i * 16 + (lane >> 4) * 4;
-          bf16x4 r4 = {};
-          if (a.res && in[i]) r4 = *reinterpret_cast<const bf16x4*>(a.res + ((long)px * a.K + n0 + c));
           bf16x4 o;
 #pragma unroll
-          for (int e = 0; e < 4; ++e) o[e] = (bf16)act(acc[i][j][e] * sc[i][e] + sh[i][e] + (float)r4[e]);
+          for (int e = 0; e < 4; ++e) o[e] = (bf16)act(acc[i][j][e] * sc[i][e] + sh[i][e] + (float)r4[i][e]);
           *reinterpret_cast<bf16x4*>(hlds + unit(pl, c >> 3) * 16 + (c & 4) * 2) = o;
         }
       }
