@@ -686,8 +686,7 @@ dstack_status dstack_op_conv2d(const void* x, int N, int H, int W, int C, const 
  *   fp32 output); fills at most max_convs, *n_convs = the total. */
 typedef struct {
   int kernel;          /* 0: tiled implicit GEMM; 1: streaming 1x1 (C <= 32); 2: 3x3 stride 1 with the tile's
-                          input pixels kept in LDS (C % 64 == 0, K % 8 == 0, bf16 output; a y that is not
-                          16-byte aligned runs kernel 0 instead) */
+                          input pixels kept in LDS (C % 64 == 0, K % 8 == 0, bf16 output) */
   int mode;            /* activation addressing: 0 1x1 strided, 1 C % 64 == 0, 2 general, 3 1x1 stride 1 */
   int tile_n, tile_m;  /* output channels x output pixels per workgroup (kernel 1: channels per wave, 0) */
   int splits;          /* depth slices (1: no split) */

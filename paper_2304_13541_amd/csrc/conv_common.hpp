@@ -138,7 +138,7 @@ struct HaloPlan {
 // false: no tile shape takes it.  C % 64 == 0.
 bool halo_plan(int N, int H, int W, int C, int K, int n_cu, bool can_split, size_t split_bytes, HaloPlan* out);
 void halo_tile(const HaloPlan& p, int* bn, int* bm, int* stages);
-// K % 8 == 0; y 16-byte aligned; a split plan needs the workspace and counters it was made for.
+// K % 8 == 0; a split plan needs the workspace and counters it was made for.
 void launch_halo(const bf16* x, int N, int H, int W, int C, const bf16* w, int K, const float* scale,
                  const float* shift, const bf16* res, int act, bf16* y, const HaloPlan& p, float* splitk_ws,
                  unsigned* tile_counters, hipStream_t st);

@@ -376,7 +376,7 @@ __global__ __launch_bounds__(64 * WN * WM * KG) void conv_halo_kernel(HaloArgs a
 #pragma unroll
     for (int k = 0; k < RPT; ++k) {
       const int px = out_pixel(p0 + k * RS);
-      if (px >= 0) *reinterpret_cast<uint4*>(a.y + ((long)px * a.K + ch)) = v[k];
+      if (px >= 0) __builtin_memcpy(a.y + ((long)px * a.K + ch), &v[k], 16);  // (any alignment: one store)
     }
     return;
   }

@@ -767,9 +767,7 @@ static dstack_status conv_shape(int N, int H, int W, int C, int K, int R, int S,
 // fused reduction stores bf16).
 //
 // 3x3 layers of stride 1 with whole 64-channel chunks may take the kernel
-// that keeps the tile's input pixels in LDS (`halo`, which a caller whose
-// output is not 16-byte aligned leaves out: that kernel stores 16 bytes at a
-// time).  The estimates are compared after a correction of the general
+// that keeps the tile's input pixels in LDS (`halo`).  The estimates are compared after a correction of the general
 // kernel's, which is about 15% low unsplit (estimate against measured less a
 // launch gap of 1.3 us: 11.5 / 12.1 to 15.2 / 19.7 us) and high for split
 // 64 x 64 tiles (10.9 / 7.6 to 14.0 / 11.4 us); the halo kernel's are within
@@ -792,7 +790,7 @@ static double general_correction(const ConvPlan& p, const ConvArgs& a) {
   return rounds > 4 ? 1.05 : 1.15;
 }
 static ConvLaunchPlan conv_launch_plan(const ConvArgs& a, bool out_fp32, bool can_split, size_t split_bytes,
-                                       HaloPlan* halo = nullptr) {
+                                       HaloPlan* halo) {
   ConvLaunchPlan L{};
   const bool one = a.R == 1 && a.S == 1 && a.pad == 0;
   if (one && a.stride == 1 && a.C <= 32 && a.K % 16 == 0 && a.act <= ACT_RELU6) {  // small depth: streaming
@@ -807,7 +805,7 @@ static ConvLaunchPlan conv_launch_plan(const ConvArgs& a, bool out_fp32, bool ca
   L.kernel = 0;
   L.mode = one ? (a.stride == 1 ? MODE_1X1S1 : MODE_1X1) : (a.C % BK == 0 && a.R * a.S <= 32 ? MODE_TILED : MODE_GENERIC);
   const ConvPlan p = choose_plan(a.M, a.K, a.Kg, a.n_cu, can_split && !out_fp32, split_bytes);
-  if (halo && a.R == 3 && a.S == 3 && a.stride == 1 && a.pad == 1 && a.C % BK == 0 && a.K % 8 == 0 && !out_fp32 &&
+  if (a.R == 3 && a.S == 3 && a.stride == 1 && a.pad == 1 && a.C % BK == 0 && a.K % 8 == 0 && !out_fp32 &&
       (p.splits == 1 ||
        (a.n_cu >= kHaloSplitCus && (size_t)p.splits * a.M * a.K * sizeof(float) <= ((size_t)32 << 20))) &&
       halo_plan(a.N, a.H, a.W, a.C, a.K, a.n_cu, can_split, split_bytes, halo) &&
@@ -857,8 +855,7 @@ dstack_status launch_conv2d_ws(const bf16* x, int N, int H, int W, int C, const 
   a.div_s = FastDiv::make(S);
   HaloPlan halo;
   const bool can_split = splitk_ws != nullptr && tile_counters != nullptr;
-  const ConvLaunchPlan p =
-      conv_launch_plan(a, out_fp32, can_split, splitk_bytes, ((uintptr_t)y & 15) == 0 ? &halo : nullptr);
+  const ConvLaunchPlan p = conv_launch_plan(a, out_fp32, can_split, splitk_bytes, &halo);
   if (p.kernel == 2) {
     launch_halo(x, N, H, W, C, w, K, scale, shift, res, act, static_cast<bf16*>(y), halo, splitk_ws, tile_counters,
                 st);

@@ -136,10 +136,17 @@ def test_conv_halo(env, case):
 
 
 @pytest.mark.gpu
-def test_unaligned_output_takes_the_general_kernel(env):
-    """A y that is 8 but not 16 bytes aligned keeps working (4-channel stores)."""
-    p, got, ref = run(env, (2, 14, 14, 128, 64, 1, False, 128), offset=4)
-    assert p["kernel"] == 2 and max(env[3].rel_err(g, ref) for g in got) <= TOL
+@pytest.mark.parametrize("case", [(2, 14, 14, 128, 64, 1, False, 128), (8, 28, 28, 128, 64, 1, True, 64),
+                                  (8, 28, 28, 128, 256, 1, True, 64), (1, 7, 7, 512, 512, 1, False, 256)],
+                         ids=["64x64", "64x128", "128x256", "split"])
+def test_unaligned_output_runs_the_planned_kernel(env, case):
+    """A y that is 8 or 2 bytes past an aligned address holds the bits of an aligned one, with the split and without
+    (the general kernel sums in another order)."""
+    p, want, ref = run(env, case)
+    assert p["kernel"] == 2 and max(env[3].rel_err(g, ref) for g in want) <= TOL
+    for offset in (4, 1):
+        _, got, _ = run(env, case, offset=offset)
+        assert all(np.array_equal(g, w) for g, w in zip(got, want)), offset
 
 
 @pytest.mark.gpu
