@@ -6,6 +6,7 @@ The cases sit at the edges of its plan: one item, a full and a just
 overfull batch slice (16 / 17), ragged slices, one depth step (H = 32), idle
 waves (H = 96), the widest rows (H = 2048), partitions that hold the rows in
 8, 4 and 2 tiles per workgroup, and engines of unequal size (5 and 10 slots).
+The plan and the control words show which path ran.
 Also: NaN inputs stay in their item, a wait that gives up at once, layers that
 share CUs, replays of a captured launch.
 
@@ -19,18 +20,18 @@ pytestmark = pytest.mark.gpu
 TOL = 2.0 ** -7
 
 CASES = [
-    # T, B, I, H, slots (None: the default stream, the whole GPU)
-    (4, 1, 8, 32, 1),
-    (5, 16, 16, 96, 2),
-    (9, 17, 24, 96, 4),
-    (6, 5, 64, 256, 6),
-    (50, 32, 40, 512, 8),
-    (12, 31, 64, 1024, 10),
-    (7, 3, 64, 1024, 5),
-    (20, 32, 64, 1024, 16),
-    (20, 16, 64, 1024, None),
-    (4, 9, 32, 1056, None),
-    (5, 16, 32, 2048, None),
+    # T, B, I, H, slots (None: the default stream, the whole GPU), row tiles per workgroup
+    (4, 1, 8, 32, 1, 2),
+    (5, 16, 16, 96, 2, 2),
+    (9, 17, 24, 96, 4, 2),
+    (6, 5, 64, 256, 6, 2),
+    (50, 32, 40, 512, 8, 4),
+    (12, 31, 64, 1024, 10, 8),
+    (7, 3, 64, 1024, 5, 8),
+    (20, 32, 64, 1024, 16, 4),
+    (20, 16, 64, 1024, None, 2),
+    (4, 9, 32, 1056, None, 2),
+    (5, 16, 32, 2048, None, 2),
 ]
 
 
@@ -83,8 +84,9 @@ class Layer:
 
 @pytest.mark.parametrize("case", CASES, ids=["-".join(str(v) for v in c) for c in CASES])
 def test_lstm_sequence(env, case):
-    T, B, I, H, slots = case
+    T, B, I, H, slots, row_tiles = case
     print("lstm sequence", case, flush=True)
+    assert env[0].lstm_plan(T, B, H, 8 * slots if slots else 256)[0] == row_tiles
     layer = Layer(env, T, B, I, H)
     part = env[0].Partition(slot_offset=0, n_slots=slots) if slots else None
     try:
@@ -97,18 +99,25 @@ def test_lstm_sequence(env, case):
     errs = [env[3].rel_err(v, ref) for v in (hb, hf)]
     print("  rel_err", errs, flush=True)
     assert max(errs) <= TOL
+    gave_up, done = layer.control()  # the one launch ran, and went through by itself
+    assert gave_up == 0 and not done.any()
 
 
 def test_scattered_slots(env):
-    """Slots of one shader engine and one of another: the plan counts what the smaller one holds."""
+    """Eight slots of one shader engine and one of another: the plan counts twice what the smaller one holds, 16
+    workgroups, all of which run at once."""
     layer = Layer(env, 6, 4, 32, 512)
-    part = env[0].Partition(slot_mask=0x11111113)
+    mask = 0x11111113
+    assert env[0].lstm_plan(6, 4, 512, 72, sum(0xff << 8 * j for j in range(32) if mask >> j & 1)) == (8, 16)
+    part = env[0].Partition(slot_mask=mask)
     try:
         layer.run(part.stream_ptr)
         hb, hf = layer.result()
     finally:
         part.destroy()
     assert env[3].rel_err(hf, layer.ref()) <= TOL
+    gave_up, done = layer.control()
+    assert gave_up == 0 and not done.any()
 
 
 def test_nan_stays_in_its_item(env):
