@@ -113,9 +113,10 @@ def sweep():
 
 def kernel_class(name):
     for key, cls in (("probe_kernel", "marker"), ("conv_igemm_1x1s", "conv_1x1_stream"), ("conv_igemm", "conv"),
-                     ("conv_halo", "conv"), ("conv_rgb", "stem"), ("expand_dw", "expand_dw"), ("dwconv3x3", "dwconv3x3"),
+                     ("conv_halo", "conv_halo"), ("conv_rgb", "stem"), ("expand_dw", "expand_dw"), ("dwconv3x3", "dwconv3x3"),
                      ("fc_reduce", "fc"), ("fc_kernel", "fc"), ("lstm_step", "lstm_step"),
-                     ("lstm_seq", "lstm_seq"), ("maxpool", "pool"), ("avgpool", "pool")):
+                     ("lstm_seq", "lstm_seq"), ("attention", "attention"), ("embed_ln", "layernorm"),
+                     ("layernorm", "layernorm"), ("maxpool", "pool"), ("avgpool", "pool")):
         if key in name:
             return cls
     return "other"
@@ -314,7 +315,7 @@ def bench_kernels(trace_dir, bench_log, ref_log=None):
     per = collections.OrderedDict((i, []) for i in range(len(BENCH_MODELS)))
     for seg, r in _segmented(csv.DictReader(open(path)), grid):
         if seg is not None and BENCH_MODEL_SEG <= seg < BENCH_MODEL_SEG + len(BENCH_MODELS):
-            if kernel_class(r["Kernel_Name"]) in ("conv", "conv_1x1_stream"):
+            if kernel_class(r["Kernel_Name"]) in ("conv", "conv_halo", "conv_1x1_stream"):
                 per[seg - BENCH_MODEL_SEG].append((int(r["End_Timestamp"]) - int(r["Start_Timestamp"])) * 1e-3)
     allv = [v for vs in per.values() for v in vs]
     bj = _bench_json(bench_log)
@@ -370,7 +371,7 @@ def bench_traffic(fetch_dir, write_dir, bench_log):
             if seg == BENCH_CAL_SEG:
                 cal[cname] += e["v"]
             elif seg is not None and BENCH_MODEL_SEG <= seg < BENCH_MODEL_SEG + len(BENCH_MODELS) and \
-                    kernel_class(e["Kernel_Name"]) in ("conv", "conv_1x1_stream"):
+                    kernel_class(e["Kernel_Name"]) in ("conv", "conv_halo", "conv_1x1_stream"):
                 tot[cname] += e["v"]
                 n[cname] += 1
     cal_kib = CALIBRATION_BYTES / 1024.0
