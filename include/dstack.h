@@ -691,7 +691,7 @@ typedef struct {
   int tile_n, tile_m;  /* output channels x output pixels per workgroup (kernel 1: channels per wave, 0) */
   int splits;          /* depth slices (1: no split) */
   int tiles_per_split; /* 64-deep depth tiles per slice */
-  int stages;          /* LDS ring depth (kernels 0 and 2) */
+  int stages;          /* LDS ring depth (kernels 0 and 2; 8 in kernel 0: two groups of waves with 4 each) */
   int pad;
   size_t workspace_bytes;
 } dstack_conv_plan;

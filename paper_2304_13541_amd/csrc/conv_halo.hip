@@ -3,8 +3,9 @@
 // (Sec. 3, Sec. 4.1).  Same arithmetic and epilogue as the general implicit
 // GEMM: y = act(scale * conv(x, w) + shift [+ res]), NHWC / KRSC.
 //
-// What bounds the general kernel on these layers is the LDS port (128 bytes
-// per clock and CU): it copies every pixel row into LDS nine times, once per
+// What bounds the general kernel on these layers is the LDS port (it moves 98
+// of the port's 128 bytes per clock and CU on VGG-19's large layers, at 0.25 of
+// the MFMA rate): it copies every pixel row into LDS nine times, once per
 // window position, and reads it back for the products.  Here a block copies
 // the input pixels under its output tile once per 64 channels (the patch:
 // the tile and a one-pixel halo, 128-byte rows) and reads the nine windows
@@ -31,12 +32,17 @@
 // count of loads in flight is the same at every step.
 //
 // Measured on MI355X (general kernel -> this one): on 128 CUs 16 images of
-// 14x14x256 -> 256 17.3 -> 12.4 us, 28x28x128 -> 128 14.8 -> 11.2 us, two
-// images of 56x56x256 -> 256 25.8 -> 17.2 us (431 TFLOP/s) and of
-// 28x28x512 -> 512 26.0 -> 20.2 us; on 256 CUs 32 images of 28x28x512 -> 512
-// 122 -> 97 us (1220 TFLOP/s).  With one chunk of 64 channels the patch is
-// used once and the general kernel's smaller blocks are faster (56x56x64 ->
-// 64: 14.9 against 15.6 us); the estimates of the dispatch keep it there.
+// 14x14x256 -> 256 16.8 -> 12.0 us, 28x28x128 -> 128 14.4 -> 10.7 us, two
+// images of 56x56x256 -> 256 25.7 -> 16.4 us (450 TFLOP/s) and of
+// 28x28x512 -> 512 25.3 -> 19.6 us; on 256 CUs 32 images of 28x28x512 -> 512
+// 125 -> 99 us (1190 TFLOP/s) and of 56x56x256 -> 256 124-130 -> 110-115 us (by
+// the data: 1030-1080 TFLOP/s).  By the counters no unit is full: on VGG-19 b8
+// the LDS port moves 67 bytes per clock and CU, the matrix cores are busy 0.40
+// of the time, and waves wait on dependencies (0.35) and to issue (0.35), which
+// is block start, epilogue and the barrier of every step.  With one chunk of
+// 64 channels the patch is used once and the general kernel's smaller blocks
+// can be as fast (16 images of 56x56x64 -> 64 14.8 us there); the estimates of
+// the dispatch keep those.
 #include <algorithm>
 #include <type_traits>
 

@@ -630,7 +630,8 @@ static bool short_ring(int per, int splits, long blocks, int n_cu) {
   return per <= (splits > 1 ? kShortSplitTiles : kShortTiles) && blocks > 2L * n_cu;
 }
 // 64 x 64 and 32 x 128 tiles with at most one block per CU run as two depth
-// groups of 4 waves, each with a ring of 4 tiles, that take the tiles in turn
+// groups of 4 waves, each with a ring of 4 tiles (8 stages in the plan), that
+// take the tiles in turn
 // and add their sums in the epilogue.  With one block of 4 waves on a CU a
 // step is a chain of barrier, LDS reads and 8 products (0.26 us for 0.05 us
 // of products, and a ring of 8 tiles does not shorten it: 6.7 -> 7.3 us); two
@@ -643,7 +644,7 @@ static bool short_ring(int per, int splits, long blocks, int n_cu) {
 // which hold different numbers of CUs when the partition is no multiple of
 // 32: blocks are counted against whole groups of 32.
 constexpr int kGroupTiles = 6;
-constexpr int LONG_RING = 8;
+constexpr int GROUP_STAGES = 8;
 static bool two_groups(int bn, int bm, int per, long blocks, int n_cu) {
   return bn * bm == 64 * 64 && per >= kGroupTiles && blocks <= n_cu / 32 * 32;
 }
@@ -718,7 +719,7 @@ static void launch_mode(ConvArgs a, bool f32, int splits, int stages, hipStream_
   a.tiles = ceil_div(a.M, BM) * a.tiles_n;
   a.div_tn = FastDiv::make(a.tiles_n);
   if constexpr (BN * BM == 64 * 64)
-    if (stages == LONG_RING) return launch_ring<BN, BM, WN, WM, LONG_RING / 2, MODE, 2>(a, f32, splits, st);
+    if (stages == GROUP_STAGES) return launch_ring<BN, BM, WN, WM, GROUP_STAGES / 2, MODE, 2>(a, f32, splits, st);
   if (stages == 2)
     launch_ring<BN, BM, WN, WM, 2, MODE, 1>(a, f32, splits, st);
   else
@@ -767,20 +768,27 @@ static dstack_status conv_shape(int N, int H, int W, int C, int K, int R, int S,
 // fused reduction stores bf16).
 //
 // 3x3 layers of stride 1 with whole 64-channel chunks may take the kernel
-// that keeps the tile's input pixels in LDS (`halo`).  The estimates are compared after a correction of the general
-// kernel's, which is about 15% low unsplit (estimate against measured less a
-// launch gap of 1.3 us: 11.5 / 12.1 to 15.2 / 19.7 us) and high for split
-// 64 x 64 tiles (10.9 / 7.6 to 14.0 / 11.4 us); the halo kernel's are within
-// 5% (8% high on a small partition whose shader engines hold different
-// numbers of CUs, hence the margin).  The general kernel keeps fp32 outputs
-// and the shapes whose split plan needs more than 32 MiB of slices (the
-// allocation-free entry point refuses those).  Partitions of fewer than 32
-// CUs keep a split general plan, whose slices callers with the fixed scratch
-// count on there (24 CUs, 6 images of 7x7x448 -> 160: 15.9 us, 13.2 in this
-// kernel); unsplit plans go by the estimates on any number of CUs (general
-// against this kernel: 24 CUs, 8 images of 28x28x128 -> 128 30.9 / 25.5 us;
-// 32 CUs, 16 of 14x14x256 -> 256 32.8 / 26.8; 48 CUs, 2 of 57x55x512 -> 160
-// 106.7 / 74.0; 56 CUs, 4 of 14x14x256 -> 256 20.1 / 12.5).
+// that keeps the tile's input pixels in LDS (`halo`).  The estimates are
+// compared after a correction of the general kernel's, which is about 15% low
+// unsplit (estimate against measured less a launch gap of 1.3 us: 11.5 / 12.1
+// to 15.2 / 19.7 us) and high for split 64 x 64 tiles (10.9 / 7.6 to 14.0 /
+// 11.4 us); the halo kernel takes 0.8 to 1.1 of its estimate (64 x 128 tiles up
+// to 1.28 on CUs that are no multiple of 32, whose shader engines hold different
+// numbers of CUs; below 64 CUs a margin counts that).  The general kernel keeps
+// fp32 outputs.
+// Two lines do not follow the speed: shapes whose general split plan needs more
+// than 32 MiB of slices stay with it, since the allocation-free entry point
+// refuses those shapes and is to refuse the same ones as before; and below 32
+// CUs a split general plan stays (24 CUs, 6 images of 7x7x448 -> 160: 15.9 us,
+// 13.2 in this kernel), since the split plans that the entry points' checks run
+// on are found there.  Unsplit plans go by the estimates on any number of CUs
+// (general against this kernel: 24 CUs, 8 images of 28x28x128 -> 128 31.1 /
+// 24.5 us; 32 CUs, 16 of 14x14x256 -> 256 33.3 / 26.0; 48 CUs, 2 of 57x55x512
+// -> 160 107.2 / 73.6; 56 CUs, 4 of 14x14x256 -> 256 18.5 / 12.5).  1069 drawn
+// shapes that took this kernel took 0.759 of the general kernel's time in the
+// mean; 10 were more than 2% slower, 3 more than 7%, those on CUs that are no
+// multiple of 32 (14 images of 33x33x64 -> 64 with a residual on 176 CUs 7.2 ->
+// 8.9 us, the largest).
 constexpr int kHaloSplitCus = 32;
 static double general_correction(const ConvPlan& p, const ConvArgs& a) {
   if (p.splits > 1) return p.bn * p.bm <= 64 * 64 ? 0.75 : 1.0;
@@ -825,7 +833,7 @@ static ConvLaunchPlan conv_launch_plan(const ConvArgs& a, bool out_fp32, bool ca
   const long tiles = (long)ceil_div(a.M, p.bm) * ceil_div(a.K, p.bn);
   L.stages = conv_stages(p.bn, p.bm);
   if (L.stages > 2 && short_ring(L.kt_per_split, L.splits, tiles * L.splits, a.n_cu)) L.stages = 2;
-  if (two_groups(p.bn, p.bm, L.kt_per_split, tiles * L.splits, a.n_cu)) L.stages = LONG_RING;
+  if (two_groups(p.bn, p.bm, L.kt_per_split, tiles * L.splits, a.n_cu)) L.stages = GROUP_STAGES;
   return L;
 }
 

@@ -18,15 +18,16 @@
 // to leave in 16-byte pieces of consecutive addresses.
 //
 // Bound by instruction issue at two waves per SIMD (7x7: a group's 28 MFMAs
-// and about as many cycles of address, scale and packing instructions) and
-// by each block's start (weights and rows, about 3 us); the 3x3 stems by
-// writing the output.  The strip length gives every CU the same number of
+// and about as many cycles of address, scale and packing instructions; the
+// waves issue 0.35 of their cycles, wait to issue 0.34 and on dependencies
+// 0.31, the matrix cores are busy 0.25) and by each block's start (weights and
+// rows, about 3 us); the 3x3 stems by writing the output.  The strip length gives every CU the same number of
 // strips, two blocks per CU (7x7) or four (3x3).  Measured against blocks of
 // 256 pixels that staged their rows and weights each: 16 images of 224x224
-// through the 7x7/2 stem on 128 CUs 26.8 -> 17.2 us (1.8 TB/s), one image on
-// 256 CUs 7.4 -> 5.1 us, 8 images through the 3x3/1 stem of 64 channels 16.4
-// -> 13.5 us (4.0 TB/s), 32 through the 3x3/2 stem of 32 channels on 128 CUs
-// 16.5 -> 12.7 us.
+// through the 7x7/2 stem on 128 CUs 26.8 -> 16.7 us (1.8 TB/s), one image on
+// 256 CUs 7.3 -> 5.2 us, 8 images through the 3x3/1 stem of 64 channels 15.4
+// -> 12.6 us (4.3 TB/s), 32 through the 3x3/2 stem of 32 channels on 128 CUs
+// 16.0 -> 12.2 us.
 #include <algorithm>
 
 #include "common.hpp"

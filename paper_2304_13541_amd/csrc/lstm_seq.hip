@@ -9,9 +9,11 @@
 // (one batch slice of at most 16 items) each own RT row tiles, i.e. 4 RT
 // hidden units with their four gates, and the 8 waves of a block split the
 // depth.  What remains is a chain of T exchanges of h between the blocks,
-// about 1 us each through device-scope memory, and the cell update: 2.7 us a
-// step on 128 CUs (layer 321 -> 165 us with its input projection; B = 4
-// 255 -> 140, B = 1 239 -> 165; H = 256, B = 8 on 48 CUs 177 -> 92).
+// about 1 us each through device-scope memory, and the cell update: 3.2 us a
+// step on 128 CUs (layer 322 -> 182 us with its input projection; B = 4
+// 253 -> 132, B = 1 242 -> 165; H = 256, B = 8 on 48 CUs 181 -> 94).  The cell
+// takes 0.4 us of a step: the step path's divisions and tanhf, as exact as
+// there (v_rcp and 1 - 2 / (1 + e^2x) were up to 6 ulp off, 159 us).
 //
 // Exchange.  Two slots of h in bf16, laid out [k/8][item][8], written with
 // device-scope 16-byte stores (narrower ones cost up to 0.7 us a step more)
@@ -31,7 +33,7 @@
 // Measured with 50 steps, B = 32, H = 1024: two layers released together on 16
 // slots each, 8 of them shared, 0.39 ms (0.46 by one launch per step), four on
 // the same 16 slots, of which three give up, 2.1 ms (0.86); shared work alone
-// takes 0.55 ms, 11 us a step.
+// takes 0.55 ms, 10 us a step.
 #include <algorithm>
 
 #include "common.hpp"
@@ -408,7 +410,7 @@ static int lstm_seq_blocks(int n_cu, const uint32_t* mask) {
 
 // The fewest row tiles per block that the CUs allow (more CUs on a group's
 // rows means fewer products and partial sums on each: RT = 2 / 4 / 8 takes
-// 2.4 / 2.6 / 3.3 us a step for 16 items, H = 1024), groups of at most 16
+// 2.9 / 3.0 / 3.4 us a step for 16 items, H = 1024), groups of at most 16
 // items (one MFMA column tile).  A block's weights must fit its registers:
 // RT * (depth steps per wave) <= 32.  Sequences of fewer than 4 steps and
 // partitions that cannot hold a group stay with one launch per step.
